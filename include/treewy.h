@@ -159,7 +159,7 @@ treewy_status treewy_commit_verify(const void *S_old, const float *U_prev, const
  * chain of T tokens per unit and return every token's output and the final
  * state.  This is the chain WY form that the tree method generalises
  * (Related work and Method: DeltaNet's chain transform): in chunks of 32
- * tokens (64 with fp32 tokens), each chunk is one chain verify (eq. 2) from
+ * tokens (64 for some sizes with fp32 tokens), each chunk is one chain verify (eq. 2) from
  * the current state, and
  * the state after its last token is rebuilt with eq. 3 and becomes the next
  * chunk's S0.  One launch on `stream`; the state stays on chip between

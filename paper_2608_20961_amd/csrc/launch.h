@@ -20,11 +20,16 @@ hipError_t launch_commit_verify(const void *S_old, const float *U_prev, const vo
                                 const int32_t *parent, int N, int B, int H, bool f32_in, bool bf16_state,
                                 void *S_new, void *o, float *U, int32_t *err, hipStream_t stream);
 
-// Chain prefill: T tokens per unit in chunks of 64, one launch, the state in
+// Chain prefill: T tokens per unit in chunks, one launch, the state in
 // registers between chunks; inputs and o are [B, H, T, ...].
 hipError_t launch_prefill(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
                           const float *beta, int T, int B, int H, bool f32_in, bool bf16_state, void *S_T, void *o,
                           int32_t *err, hipStream_t stream);
+
+// ... by one four-wave workgroup per unit (launch_prefill uses it for some sizes).
+hipError_t launch_prefill_unit(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
+                               const float *beta, int T, int B, int H, bool f32_in, bool bf16_state, void *S_T,
+                               void *o, int32_t *err, hipStream_t stream);
 
 hipError_t launch_commit(const void *S0, const float *U, const void *k, const float *alpha,
                          const int32_t *path, const int32_t *path_len, int L_max,

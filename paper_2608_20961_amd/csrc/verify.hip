@@ -1609,14 +1609,15 @@ hipError_t launch_commit_verify(const void *S_old, const float *U_prev, const vo
                           stream);
 }
 
-// Chain prefill: every chunk of every unit in one launch, the state kept in
-// registers between chunks (see treewy_chain_prefill).  bf16 tokens run in
+// Chain prefill with one workgroup per unit (prefill.hip says for which sizes):
+// every chunk of every unit in one launch, the state kept in registers
+// between chunks (see treewy_chain_prefill).  bf16 tokens run in
 // 32-token chunks: the 32-row kernel has the registers to fetch the next
 // chunk during the current one, and its solve is short.  fp32 tokens run in
 // 64-token chunks at one workgroup per CU, also fetching ahead.
-hipError_t launch_prefill(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
-                          const float *beta, int T, int B, int H, bool f32_in, bool bf16_state, void *S_T, void *o,
-                          int32_t *err, hipStream_t stream) {
+hipError_t launch_prefill_unit(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
+                               const float *beta, int T, int B, int H, bool f32_in, bool bf16_state, void *S_T, void *o,
+                               int32_t *err, hipStream_t stream) {
     CommitArgs cm = {};
     cm.S_new = S_T;
     if (bf16_state)
