@@ -1,4 +1,5 @@
-"""Build libtreewy.so from csrc/ with hipcc for gfx950 (in-tree).
+"""Build libtreewy.so from csrc/ with hipcc for gfx950, and the Python binding's native call path (_binding.so, host
+code only) against the installed torch (both in-tree).
 
     python -m paper_2608_20961_amd.build
 """
@@ -14,6 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libtreewy.so")
+BINDING = os.path.join(PKG, "_binding.so")
 SOURCES = ["api.hip", "verify.hip", "prefill.hip", "commit.hip", "snapshot.hip", "tree.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -23,9 +25,34 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-I", INCLUDE, "-I", CSRC]
 
 
+def binding_command(obj: str) -> list:
+    """g++ over binding.cpp (no device code) with torch's and HIP's headers."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include", INCLUDE]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-w", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *[x for i in inc for x in ("-isystem", i)],
+            "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj]
+
+
+def link_binding(obj: str) -> None:
+    """Links the binding; torch's libraries and libtreewy.so are in the process when it is imported."""
+    from torch.utils import cpp_extension
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    libs = [x for d in cpp_extension.library_paths() for x in ("-L", d, "-Wl,-rpath-link," + d)]
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", tmp, obj, "-L", PKG, "-Wl,-rpath,$ORIGIN", "-l:libtreewy.so", *libs,
+                    "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"], check=True)
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     procs = []
+    binding_obj = os.path.join(OBJDIR, "binding.o")
+    procs.append(("binding.cpp", subprocess.Popen(binding_command(binding_obj), stdout=subprocess.PIPE,
+                                                  stderr=subprocess.STDOUT, text=True)))
     objs = []
     for src in SOURCES:
         obj = os.path.join(OBJDIR, src.replace(".hip", ".o"))
@@ -47,6 +74,7 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB)
+    link_binding(binding_obj)
     return LIB
 
 

@@ -1,10 +1,14 @@
-"""Python binding of libtreewy.so (ctypes).  Argument marshalling only.
+"""Python binding of libtreewy.so.  Argument marshalling only.
 
 Every computation runs in the HIP kernels behind the C ABI declared in
 include/treewy.h; this module checks tensor shapes, dtypes and devices,
 allocates outputs with PyTorch when the caller gives none, and passes raw
 device pointers and the current HIP stream.  There is no CPU fallback: if the
 library has not been built, importing this module raises.
+
+The calls of a serving loop go through a native call path (csrc/binding.cpp),
+which does all of this in one step where every argument is acceptable; a call
+that it does not take runs through the checks here, which name what is wrong.
 
 Function names match the C ABI:
   treewy_verify(S0, q, k, v, alpha, beta, parent) -> (o, U)
@@ -32,6 +36,7 @@ if not os.path.exists(LIB_PATH):
     raise ImportError("libtreewy.so is not built; run `python -m paper_2608_20961_amd.build` first")
 
 lib = ctypes.CDLL(LIB_PATH)
+from . import _binding  # noqa: E402  (after the library it calls)
 
 TREEWY_OK, TREEWY_ERR_INVALID_ARG, TREEWY_ERR_UNSUPPORTED, TREEWY_ERR_HIP = 0, 1, 2, 3
 TREEWY_F32, TREEWY_BF16 = 0, 1
@@ -66,6 +71,13 @@ class TreewyError(RuntimeError):
     def __init__(self, status: int, call: str):
         super().__init__("%s: %s (status %d)" % (call, lib.treewy_status_string(status).decode(), status))
         self.status = status
+
+
+def _taken(r, call: str) -> bool:
+    """Whether the native path took the call (None: it did not); raises where the library refused it."""
+    if type(r) is int:
+        raise TreewyError(r, call)
+    return r is not None
 
 
 def _check(status: int, call: str) -> None:
@@ -117,6 +129,9 @@ def _in_dtype(t: torch.Tensor) -> int:
 
 def treewy_verify(S0, q, k, v, alpha, beta, parent, o=None, U=None, err=None, stream=None
                   ) -> Tuple[torch.Tensor, torch.Tensor]:
+    r = _binding.verify(S0, q, k, v, alpha, beta, parent, o, U, err, stream)
+    if _taken(r, "treewy_verify"):
+        return r
     B, H, N, dk = q.shape
     dv = v.shape[-1]
     dt = q.dtype
@@ -140,6 +155,9 @@ def treewy_verify(S0, q, k, v, alpha, beta, parent, o=None, U=None, err=None, st
 
 def treewy_commit(S0, U, k, alpha, path, path_len, parent=None, S_new=None, err=None, stream=None
                   ) -> torch.Tensor:
+    r = _binding.commit(S0, U, k, alpha, path, path_len, parent, S_new, err, stream)
+    if _taken(r, "treewy_commit"):
+        return r
     B, H, N, dk = k.shape
     dv = U.shape[-1]
     L_max = path.shape[1]
@@ -162,6 +180,10 @@ def treewy_commit(S0, U, k, alpha, path, path_len, parent=None, S_new=None, err=
 def treewy_commit_verify(S_old, U_prev, k_prev, alpha_prev, path, path_len, q, k, v, alpha, beta, parent,
                          parent_prev=None, S_new=None, o=None, U=None, err=None, stream=None
                          ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
+    r = _binding.commit_verify(S_old, U_prev, k_prev, alpha_prev, path, path_len, q, k, v, alpha, beta, parent,
+                               parent_prev, S_new, o, U, err, stream)
+    if _taken(r, "treewy_commit_verify"):
+        return r
     B, H, N, dk = q.shape
     dv = v.shape[-1]
     N_prev = k_prev.shape[2]
@@ -251,6 +273,9 @@ def treewy_path_from_node(parent, accepted, L_max, path=None, path_len=None, err
 
 def treewy_accept_greedy(parent, draft_token, target_token, root_token, L_max: int, path=None, path_len=None,
                          bonus=None, err=None, stream=None) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
+    r = _binding.accept_greedy(parent, draft_token, target_token, root_token, L_max, path, path_len, bonus, err, stream)
+    if _taken(r, "treewy_accept_greedy"):
+        return r
     B, N = parent.shape
     _need(parent, "parent", torch.int32, (B, N))
     _need(draft_token, "draft_token", torch.int32, (B, N))
@@ -278,6 +303,9 @@ def treewy_chain_prefill(S0, q, k, v, alpha, beta, S_T=None, o=None, err=None, s
     """Gated delta rule over a chain of T tokens per unit (chunks of 32 tokens,
     64 for some sizes with fp32 tokens; one launch): returns the final state and every
     token's output."""
+    r = _binding.chain_prefill(S0, q, k, v, alpha, beta, S_T, o, err, stream)
+    if _taken(r, "treewy_chain_prefill"):
+        return r
     B, H, T, dk = q.shape
     dv = v.shape[-1]
     dt = q.dtype

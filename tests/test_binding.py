@@ -1,0 +1,106 @@
+"""The native call path (csrc/binding.cpp) takes exactly the calls that the
+Python checks accept: what it does not take runs through them and raises what
+they raise, and what both can run gives the same outputs."""
+import numpy as np
+import pytest
+import torch
+
+
+def test_cpu_tensors_are_left_to_the_checks():
+    from paper_2608_20961_amd import treewy as tw
+    x = torch.zeros(1, 1, 2, 128)
+    g = torch.zeros(1, 1, 2)
+    par = torch.zeros(1, 2, dtype=torch.int32)
+    assert tw._binding.verify(torch.zeros(1, 1, 128, 128), x, x, x, g, g, par, None, None, None, None) is None
+    assert tw._binding.commit(None, x, x, g, par, par, None, None, None, None) is None
+    assert tw._binding.chain_prefill(*[x] * 8, None, None) is None
+    assert tw._binding.accept_greedy(par, par, par, par, 2, None, None, None, None, None) is None
+    with pytest.raises(ValueError, match="must be on a GPU"):
+        tw.treewy_verify(torch.zeros(1, 1, 128, 128), x, x, x, g, g, par)
+    with pytest.raises(TypeError):
+        tw._binding.verify(x)
+
+
+class Wrapped(torch.Tensor):
+    """A subclass: left to Python, which takes any tensor."""
+
+
+@pytest.fixture(scope="module")
+def case():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2608_20961_amd import treewy as tw
+    g = torch.Generator(device="cuda").manual_seed(4)
+    B, H, N = 2, 3, 9
+    unit = lambda x: x / x.norm(dim=-1, keepdim=True)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x = dict(S0=0.2 * r(B, H, 128, 128), q=unit(r(B, H, N, 128)).bfloat16(), k=unit(r(B, H, N, 128)).bfloat16(),
+             v=r(B, H, N, 128).bfloat16(), alpha=0.9 + 0.09 * torch.rand(B, H, N, generator=g, device="cuda"),
+             beta=0.1 + 0.8 * torch.rand(B, H, N, generator=g, device="cuda"),
+             parent=torch.tensor(np.tile(np.arange(-1, N - 1, dtype=np.int32) // 2, (B, 1)), device="cuda"))
+    x["parent"] = torch.where(x["parent"] >= torch.arange(N, device="cuda"), -1, x["parent"]).int().contiguous()
+    return tw, x
+
+
+@pytest.mark.gpu
+def test_native_and_python_paths_agree(case, monkeypatch):
+    tw, x = case
+    B, H, N = x["alpha"].shape
+    ver = [x[n] for n in ("S0", "q", "k", "v", "alpha", "beta", "parent")]
+    tok = [torch.randint(0, 3, s, dtype=torch.int32, device="cuda") for s in ((B, N), (B, N), (B,))]
+
+    def calls(**kw):
+        o, U = tw.treewy_verify(*ver, **kw)
+        path, plen, bonus = tw.treewy_accept_greedy(x["parent"], *tok, N, **kw)
+        S = tw.treewy_commit(x["S0"], U, x["k"], x["alpha"], path, plen, parent=x["parent"], **kw)
+        f = tw.treewy_commit_verify(x["S0"], U, x["k"], x["alpha"], path, plen, *ver[1:], parent_prev=x["parent"], **kw)
+        p = tw.treewy_chain_prefill(*ver[:6], **kw)
+        torch.cuda.synchronize()
+        return (o, U, path, plen, bonus, S, *f, *p)
+
+    native = calls()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    on_stream = calls(stream=side)
+    refuse = lambda *a: None
+    for n in ("verify", "commit", "commit_verify", "chain_prefill", "accept_greedy"):
+        monkeypatch.setattr(tw._binding, n, refuse)
+    python = calls()
+    for i, (a, b, c) in enumerate(zip(native, on_stream, python)):
+        assert a.dtype == c.dtype and a.shape == c.shape, i
+        assert torch.equal(a, b) and torch.equal(a, c), "output %d" % i
+
+
+@pytest.mark.gpu
+def test_outputs_given_are_the_ones_returned(case):
+    tw, x = case
+    ver = [x[n] for n in ("S0", "q", "k", "v", "alpha", "beta", "parent")]
+    o, U = torch.empty_like(x["v"]), torch.empty(x["v"].shape, device="cuda")
+    err = torch.zeros(x["v"].shape[0], dtype=torch.int32, device="cuda")
+    ro, rU = tw.treewy_verify(*ver, o=o, U=U, err=err)
+    assert ro is o and rU is U and int(err.sum()) == 0
+
+
+@pytest.mark.gpu
+def test_refused_calls_raise_as_the_checks_do(case):
+    tw, x = case
+    ver = {n: x[n] for n in ("S0", "q", "k", "v", "alpha", "beta", "parent")}
+
+    def bad(**kw):
+        return tw.treewy_verify(**{**ver, **kw})
+
+    with pytest.raises(ValueError, match="must be contiguous"):
+        bad(S0=x["S0"].transpose(2, 3))
+    with pytest.raises(ValueError, match="must have shape"):
+        bad(beta=x["beta"][:, :, :-1].contiguous())
+    with pytest.raises(TypeError, match="parent must be"):
+        bad(parent=x["parent"].long())
+    with pytest.raises(TypeError, match="must be float32 or bfloat16"):
+        bad(S0=x["S0"].half())
+    with pytest.raises(ValueError, match="on a GPU"):
+        bad(alpha=x["alpha"].cpu())
+    with pytest.raises(tw.TreewyError) as e:             # a bf16 state with fp32 tokens: the library's own refusal
+        bad(S0=x["S0"].bfloat16(), q=x["q"].float(), k=x["k"].float(), v=x["v"].float())
+    assert e.value.status == tw.TREEWY_ERR_UNSUPPORTED
+    o, _ = bad(q=x["q"].as_subclass(Wrapped))            # taken through Python
+    assert torch.equal(o.as_subclass(torch.Tensor), bad()[0])
