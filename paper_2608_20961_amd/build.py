@@ -16,7 +16,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libtreewy.so")
 BINDING = os.path.join(PKG, "_binding.so")
-SOURCES = ["api.hip", "verify.hip", "prefill.hip", "commit.hip", "snapshot.hip", "tree.hip"]
+SOURCES = ["api.hip", "verify.hip", "small.hip", "prefill.hip", "commit.hip", "snapshot.hip", "tree.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",

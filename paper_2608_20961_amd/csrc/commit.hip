@@ -203,6 +203,10 @@ hipError_t launch_commit(const void *S0, const float *U, const void *k, const fl
                          const int32_t *parent, int N, int B, int H, bool f32_k, bool bf16_state,
                          void *S_new, int32_t *err, hipStream_t stream) {
     const int units = B * H;
+    if (small_commit_fits(N, L_max, units)) {
+        const CommitArgs cm = {U, k, alpha, path, path_len, parent, S_new, L_max, N, N, N};
+        return launch_small_commit(S0, B, H, f32_k, bf16_state, err, cm, stream);
+    }
     const size_t lds = (size_t)2 * (L_max < STAGE_ROWS ? L_max : STAGE_ROWS) * D * sizeof(float);
     // fp32 state: a grid of resident workgroups (as many as fit on the GPU),
     // each walking units, so a workgroup starts the next unit's state reads as

@@ -24,20 +24,13 @@
 // repeated.
 #include "device.h"
 #include "launch.h"
+#include "mfma16.h"
 
 namespace treewy {
 
 namespace {
 
 constexpr int CT = 32;                                   // tokens per chunk
-
-// D(16x16) += A(16x32) B(32x16) on the matrix cores, bf16 in, fp32 accumulate.
-// Lane l supplies row l%16 of A and column l%16 of B, each with the eight
-// contraction indices of group l/16; lane l receives column l%16 of D at rows
-// 4*(l/16) + r in accumulator element r.
-__device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 
 // Order of a contraction index (d_k, or the chunk's tokens) in LDS: within
 // each 32, entry 16 h + 4 g + r sits at position 8 g + 4 h + r.  Lane group g
@@ -75,51 +68,10 @@ struct Slot {
 // consecutive rows to four different groups of four granules.
 __device__ __forceinline__ int swz(int t) { return ((t & 3) << 2) | ((t >> 2) & 3); }
 
-// Four floats -> bf16 hi + lo (see split8).
-__device__ __forceinline__ void split4(f32x4 x, uint2 &hi, uint2 &lo) {
-    hi.x = pack_bf2(x[0], x[1]);
-    hi.y = pack_bf2(x[2], x[3]);
-    lo.x = pack_bf2(x[0] - __builtin_bit_cast(float, hi.x << 16), x[1] - __builtin_bit_cast(float, hi.x & 0xffff0000u));
-    lo.y = pack_bf2(x[2] - __builtin_bit_cast(float, hi.y << 16), x[3] - __builtin_bit_cast(float, hi.y & 0xffff0000u));
-}
-
 // LDS written and read again by the same wave: the hardware keeps a wave's
 // LDS accesses in order; this keeps the compiler from reordering accesses of
 // different types.
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
-
-// r[j] += x * (b[j] of lane I of each row of 16 lanes), j = 0 .. NJ - 1: the row
-// broadcast rides on the multiply-add (the compiler leaves it a move of its
-// own).  (A DPP source must have been written two wait states before: s_nop.)
-template <int I, int NJ> __device__ __forceinline__ void fmac_bcast(float *r, const float *b, float x) {
-    static_assert(NJ == 4 || NJ == 8, "groups of four or eight");
-#define TW_F(n, m) "v_fmac_f32_dpp %" #n ", %" #m ", %[x] row_newbcast:%[i] row_mask:0xf bank_mask:0xf\n\t"
-    if constexpr (NJ == 4)
-        asm("s_nop 1\n\t" TW_F(0, 4) TW_F(1, 5) TW_F(2, 6) TW_F(3, 7)
-            : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3])
-            : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), [x] "v"(x), [i] "n"(I));
-    else
-        asm("s_nop 1\n\t" TW_F(0, 8) TW_F(1, 9) TW_F(2, 10) TW_F(3, 11) TW_F(4, 12) TW_F(5, 13) TW_F(6, 14) TW_F(7, 15)
-            : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7])
-            : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]), [x] "v"(x),
-              [i] "n"(I));
-#undef TW_F
-}
-
-// Column I of the sweep that builds row t of a 16-row diagonal block of
-// T = (I + B)^{-1}, then the next column down (the recurrence of verify.hip's
-// dense sweep, in the same order).  Row I of B comes from lane I's registers,
-// so the sweep reads no LDS.  The multiply-adds go in groups of four or
-// eight columns: those at or past I add x times a zero of B.
-template <int I> __device__ __forceinline__ void sweep16(float (&r)[16], const float (&b)[16], int t) {
-    const float x = I < t ? -r[I] : 0.f;                 // T[t, I] (zero on and above the diagonal)
-    r[I] = x;
-    if constexpr (I > 0) {
-        fmac_bcast<I, (I > 4 ? 8 : 4)>(r, b, x);
-        if constexpr (I > 8) fmac_bcast<I, (I > 12 ? 8 : 4)>(r + 8, b + 8, x);
-        sweep16<I - 1>(r, b, t);
-    }
-}
 
 // Waves of a workgroup by role.  Waves go round the CU's four SIMDs; with two
 // state waves the workgroup is launched with eight, of which waves 4 and 5
@@ -538,7 +490,6 @@ __global__ __launch_bounds__(64 * launched_waves<NS>(PW), (launched_waves<NS>(PW
                 // Rows 4 g + e of T0, column tl (a transposed read), and of T1, row tl.
                 typedef short s16x4 __attribute__((ext_vector_type(4)));
                 typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
-                auto low8 = [](uint2 x) { return __builtin_bit_cast(bf16x8, make_uint4(x.x, x.y, 0u, 0u)); };
                 const unsigned char *t0 = th + (4 * g + (tl >> 2)) * L::TS * 2 + 16 * (tl & 3);
                 const unsigned char *t1 = th + ((16 + tl) * L::TS + 8 * g + 4) * 2;
                 const bf16x8 t0h = low8(__builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)t0)));
@@ -576,14 +527,6 @@ __global__ __launch_bounds__(64 * launched_waves<NS>(PW), (launched_waves<NS>(PW
     }
 }
 
-int compute_units() {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
-    return cus;
-}
-
 template <bool F32IN, bool SBF, int NS, int PW>
 hipError_t launch(const void *S0, const void *q, const void *k, const void *v, const float *alpha, const float *beta,
                   int T, int units, int cus, void *S_T, void *o, hipStream_t stream) {
@@ -605,7 +548,7 @@ hipError_t launch(const void *S0, const void *q, const void *k, const void *v, c
 // against verify.hip's kernel, one workgroup of four like waves per unit) and
 // 2.2 to 2.5 us with a whole one (32 sequences of 1000 tokens, 64 heads, bf16
 // state: 812 -> 649 us).
-//   bf16 tokens, one chunk: verify.hip's kernel, whose chunk is bit for bit a verify.
+//   bf16 tokens, one chunk: the kernels of verify.hip and small.hip, whose chunk is bit for bit a verify.
 //   Whole units of few chunks: it too, two of its workgroups per CU hide the
 //     latency of a short unit (512 units of 64 tokens: 25.4 against 26.5 us; of
 //     512 tokens: 124 against 105 us; in one round of at most as many units as
@@ -616,6 +559,8 @@ hipError_t launch_prefill(const void *S0, const void *q, const void *k, const vo
                           const float *beta, int T, int B, int H, bool f32_in, bool bf16_state, void *S_T, void *o,
                           int32_t *err, hipStream_t stream) {
     const int units = B * H, cus = compute_units();
+    if (small_prefill_fits(T, units, f32_in))
+        return launch_small_prefill(S0, q, k, v, alpha, beta, T, B, H, bf16_state, S_T, o, stream);
     const bool quarters = (int64_t)units * 4 <= cus, halves = (int64_t)units * 2 <= cus;
     const int chunks = (T + CT - 1) / CT;
     const bool whole = !f32_in && chunks >= (units <= cus ? 2 : 5);

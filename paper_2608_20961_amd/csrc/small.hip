@@ -1,0 +1,590 @@
+// Few units: drafts of at most 16 nodes (treewy_verify, treewy_commit_verify),
+// chains of at most 16 tokens (treewy_chain_prefill) and treewy_commit: the system
+// of verify.hip on 16-row tiles, every wave on its own.  Bound by the latency of
+// the wave's reads and of its steps.
+//
+// A wave owns 16 columns of d_v (16 rows of the state) of one unit and needs
+// nothing of the other seven: K and Q rows come from memory in operand
+// layout, and the gram tiles, the ancestors and T = (I + B)^{-1} are so small
+// at 16 nodes that every wave forms its own.  So there is no LDS and no
+// barrier, and the chain of a wave is: its reads, the walk and the gram while
+// the state arrives, the sweep for T in registers, P, U = T R, O, the stores.
+// The four 16-lane rows of a wave hold the tree four times over (lane % 16 =
+// node): the sweep broadcasts within a row, and what lane group g needs of
+// nodes 4 g .. 4 g + 3 is in its own row.
+//
+// Contraction order: slots 8 g + e of a 16x16x32 product over d_k are
+// d_k 32 s + 8 g + e; over the nodes, slots e < 4 of lane group g are node 4 g +
+// e, what an accumulator tile holds, and slots e >= 4 are empty.
+#include "device.h"
+#include "launch.h"
+#include "mfma16.h"
+
+namespace treewy {
+
+namespace {
+
+constexpr int VERIFY = 0, FUSED = 1, PREFILL = 2;
+constexpr int NW = 4;                                    // waves per workgroup
+constexpr int PARTS = D / 16 / NW;                       // workgroups per unit
+
+// Value x[r] of lane group gg (0 .. 3) in every group, for the four groups of each lane % 16:
+// out[4 gg + r].
+__device__ __forceinline__ void all_groups(const f32x4 &x, float (&out)[16]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float xr = x[r];
+        const int v = __builtin_bit_cast(int, xr);
+        const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // groups 0, 0, 2, 2 and 1, 1, 3, 3
+        const int even = p[0], odd = p[1];
+        const auto a = __builtin_amdgcn_permlane32_swap(even, even, false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(odd, odd, false, false);
+        const int g0 = a[0], g2 = a[1], g1 = b[0], g3 = b[1];
+        out[r] = __builtin_bit_cast(float, g0);
+        out[4 + r] = __builtin_bit_cast(float, g1);
+        out[8 + r] = __builtin_bit_cast(float, g2);
+        out[12 + r] = __builtin_bit_cast(float, g3);
+    }
+}
+
+__device__ __forceinline__ void floats8(uint4 a, uint4 b, float (&x)[8]) {
+    const f32x4 f = __builtin_bit_cast(f32x4, a), h = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        x[e] = f[e];
+        x[4 + e] = h[e];
+    }
+}
+
+// A wave's rows of the state: lane (l16, g) holds d_k 32 s + 8 g + [0, 8) of row `col`.
+template <bool SBF>
+struct State {
+    static constexpr int SB = SBF ? 2 : 4, SN = SBF ? 1 : 2;     // bytes per entry, 16-byte pieces per eight
+    uint4 x[4][SN];
+    int col, g;
+    __device__ __forceinline__ State(int col, int g) : col(col), g(g) {}
+
+    __device__ __forceinline__ void load(const void *S0, int u) {
+        const rsrc_t rs = make_rsrc(static_cast<const char *>(S0) + (size_t)u * D * D * SB, D * D * SB);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int p = 0; p < SN; ++p) x[s][p] = ld_u32x4<CACHED>(rs, (col * D + 32 * s + 8 * g) * SB + 16 * p);
+    }
+    __device__ __forceinline__ void get(float (&f)[4][8], float scale) const {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if constexpr (SBF) {
+                const uint32_t w[4] = {x[s][0].x, x[s][0].y, x[s][0].z, x[s][0].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    f[s][2 * e] = scale * __builtin_bit_cast(float, w[e] << 16);
+                    f[s][2 * e + 1] = scale * __builtin_bit_cast(float, w[e] & 0xffff0000u);
+                }
+            } else {
+                floats8(x[s][0], x[s][SN - 1], f[s]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) f[s][e] *= scale;
+            }
+        }
+    }
+    __device__ __forceinline__ void put(const float (&f)[4][8]) {   // (a bf16 state is rounded here)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if constexpr (SBF) {
+                x[s][0] = __builtin_bit_cast(uint4, round8(f[s]));
+            } else {
+                x[s][0] = __builtin_bit_cast(uint4, f32x4{f[s][0], f[s][1], f[s][2], f[s][3]});
+                x[s][SN - 1] = __builtin_bit_cast(uint4, f32x4{f[s][4], f[s][5], f[s][6], f[s][7]});
+            }
+        }
+    }
+    // Out: an fp32 state's 16-byte pieces go round the lane groups first, so
+    // that each store instruction writes 64 bytes of a row together.
+    __device__ __forceinline__ void store(void *S_new, int u) const {
+        const rsrc_t rn = make_rsrc(static_cast<char *>(S_new) + (size_t)u * D * D * SB, D * D * SB);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if constexpr (SBF) {
+                st_u32x4<CACHED>(rn, (col * D + 32 * s + 8 * g) * SB, x[s][0]);
+            } else {                                     // pieces 2 g, 2 g + 1 of eight -> pieces g and 4 + g
+                uint32_t a[4] = {x[s][0].x, x[s][0].y, x[s][0].z, x[s][0].w};
+                uint32_t c[4] = {x[s][1].x, x[s][1].y, x[s][1].z, x[s][1].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const auto i = __builtin_amdgcn_permlane16_swap(a[e], c[e], false, false);   // pieces 0 1 4 5 | 2 3 6 7
+                    const uint32_t i0 = i[0], i1 = i[1];
+                    const auto j = __builtin_amdgcn_permlane32_swap(i0, i1, false, false);       // pieces 0 1 2 3 | 4 5 6 7
+                    a[e] = j[0];
+                    c[e] = j[1];
+                }
+                const int off = (col * D + 32 * s + 4 * g) * 4;
+                st_u32x4<CACHED>(rn, off, make_uint4(a[0], a[1], a[2], a[3]));
+                st_u32x4<CACHED>(rn, off + 64, make_uint4(c[0], c[1], c[2], c[3]));
+            }
+        }
+    }
+};
+
+// Key rows, NK at a time so that one latency covers them, each with a factor of this lane's column.
+template <bool F32IN, int NK>
+struct Keys {
+    static constexpr int XN = F32IN ? 2 : 1, SZ = F32IN ? 4 : 2;
+    uint4 k[NK][4][XN];
+    float u[NK];
+    __device__ __forceinline__ void load(int e, rsrc_t r, int row, int g) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int p = 0; p < XN; ++p) k[e][s][p] = ld_u32x4<CACHED>(r, row + (32 * s + 8 * g) * SZ + 16 * p);
+    }
+    // x[s][i] += wu k[32 s + 8 g + i]
+    __device__ __forceinline__ void rank1(float (&x)[4][8], float wu, int e) const {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            float k8[8];
+            if constexpr (F32IN) {
+                floats8(k[e][s][0], k[e][s][XN - 1], k8);
+            } else {
+                const uint32_t w[4] = {k[e][s][0].x, k[e][s][0].y, k[e][s][0].z, k[e][s][0].w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    k8[2 * i] = __builtin_bit_cast(float, w[i] << 16);
+                    k8[2 * i + 1] = __builtin_bit_cast(float, w[i] & 0xffff0000u);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[s][i] = fmaf(wu, k8[i], x[s][i]);
+        }
+    }
+};
+
+// An accepted path of at most 64 nodes of a draft of at most 64 (lane l = entry
+// l; alpha and parent of node = lane).
+struct Path {
+    rsrc_t rk, ru;
+    int len, node, par, row;
+    float al, w, ga;                                     // w: of entry l; ga: the product of alpha over the path
+
+    __device__ __forceinline__ void issue(const CommitArgs &cm, int u, int b, int in_size) {
+        const int lane = threadIdx.x & 63, np = cm.N_prev;
+        row = D * in_size;
+        rk = make_rsrc(static_cast<const char *>(cm.k) + (size_t)u * cm.in_stride * row, np * row);
+        ru = make_rsrc(cm.U + (size_t)u * cm.u_stride * D, np * D * 4);
+        al = ld_f32(make_rsrc(cm.alpha + (size_t)u * cm.in_stride, np * 4), lane * 4);
+        // (an opaque zero offset: a uniform load's result would be moved to a scalar register at once)
+        len = ld_i32(make_rsrc(cm.path_len + b, 4), opaque(0));
+        node = ld_i32(make_rsrc(cm.path + (size_t)b * cm.L_max, cm.L_max * 4), lane * 4);
+        const int32_t *pp = cm.parent;
+        par = ld_i32(make_rsrc(pp ? pp + (size_t)b * np : nullptr, pp ? np * 4 : 0), lane * 4);
+    }
+    // Entry l lies in [0, N), follows entry l - 1 in index order and (with a
+    // parent array) is its child, entry 0 a child of the committed prefix.  A
+    // bad path commits nothing.
+    __device__ __forceinline__ void check(const CommitArgs &cm, int b, bool first, int32_t *err) {
+        const int lane = threadIdx.x & 63;
+        const bool len_ok = len >= 0 && len <= cm.L_max;
+        const int n = len_ok ? len : 0;
+        const int a = lane < n ? node : -1;
+        const int before = __shfl(a, lane > 0 ? lane - 1 : 0);
+        const int pa = lane == 0 ? -1 : before;
+        const int src = (a >= 0 && a < 64) ? a : lane;
+        const int par_a = __shfl(par, src);
+        const float al_a = __shfl(al, src);
+        bool bad = !len_ok;
+        if (lane < n) bad = bad || a < 0 || a >= cm.N_prev || a <= pa || (cm.parent && par_a != pa);
+        const bool ok = !__any(bad);
+        len = __builtin_amdgcn_readfirstlane(ok ? n : 0);
+        if (!ok && first && lane == 0) flag_error(err, b, TREEWY_FLAG_BAD_PATH);
+        float x = lane < len ? al_a : 1.f;               // suffix products of the gates
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const float y = __shfl_down(x, off);
+            x *= lane + off < 64 ? y : 1.f;
+        }
+        const float after = __shfl_down(x, 1);
+        w = lane < len ? (lane + 1 < 64 ? after : 1.f) : 0.f;
+        ga = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+    }
+    // Entries l0 .. of the path (past it: an offset past the end, which reads zero).
+    template <bool F32IN, int NK>
+    __device__ __forceinline__ void load(Keys<F32IN, NK> &x, int l0, int g, int col) const {
+        constexpr int OOB = 1 << 30;
+#pragma unroll
+        for (int e = 0; e < NK; ++e) {
+            const bool live = l0 + e < len;              // (uniform)
+            const int a = __builtin_amdgcn_readlane(node, (l0 + e) & 63);
+            x.load(e, rk, live ? a * row : OOB, g);
+            x.u[e] = ld_f32(ru, live ? (a * D + col) * 4 : OOB);
+        }
+    }
+    __device__ __forceinline__ float weight(int l) const {
+        return l < len ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), l & 63)) : 0.f;
+    }
+};
+
+// S <- g_a S + sum_l w_l U_l k_l^T over the path, whose first entries are in `keys`.
+template <bool F32IN, bool SBF, int NK>
+__device__ __forceinline__ void commit_path(State<SBF> &st, const Path &path, Keys<F32IN, NK> &keys) {
+    if (path.len == 0) return;                           // (uniform; the state stays as it is, bit for bit)
+    float x[4][8];
+    st.get(x, path.ga);
+    for (int l0 = 0; l0 < path.len; l0 += NK) {
+        if (l0 > 0) path.template load<F32IN>(keys, l0, st.g, st.col);
+#pragma unroll
+        for (int e = 0; e < NK; ++e) keys.rank1(x, path.weight(l0 + e) * keys.u[e], e);
+    }
+    st.put(x);
+}
+
+template <bool F32IN, bool SBF, int MODE>
+__global__ __launch_bounds__(64 * NW) void small_kernel(
+    const void *S0, const void *__restrict__ q_, const void *__restrict__ k_, const void *__restrict__ v_,
+    const float *__restrict__ alpha, const float *__restrict__ beta, const int32_t *__restrict__ parent, int N, int H,
+    int units, void *__restrict__ o_, float *U, int32_t *__restrict__ err, CommitArgs cm) {
+    using In = typename std::conditional<F32IN, float, __bf16>::type;
+    static_assert(!(SBF && F32IN), "a bf16 state is paired with bf16 inputs");
+    constexpr int ROW = D * (int)sizeof(In);
+    // A unit's workgroups sit on one XCD (consecutive workgroups go round the
+    // eight), so that its K and Q rows are read from memory once.
+    const int bx = blockIdx.x & 7, by = blockIdx.x >> 3;
+    const int part = by % PARTS, u = (by / PARTS) * 8 + bx;
+    if (u >= units) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+    const int b = u / H, col = 16 * (part * NW + wave) + l16;    // this lane's d_v column (= row of the state)
+    State<SBF> st(col, g);
+    const bool first = part == 0 && wave == 0;                   // the wave that reports what is malformed
+    const size_t node0 = (size_t)u * N;
+
+    // ---- every read of the wave, in the order it needs them -------------------
+    int par = 0;
+    if constexpr (MODE != PREFILL) par = ld_i32(make_rsrc(parent + (size_t)b * N, N * 4), l16 * 4);
+    const float al = ld_f32(make_rsrc(alpha + node0, N * 4), l16 * 4);
+    const float be = ld_f32(make_rsrc(beta + node0, N * 4), l16 * 4);
+    Path path;
+    if constexpr (MODE == FUSED) path.issue(cm, u, b, sizeof(In));
+    const rsrc_t rk = make_rsrc(static_cast<const In *>(k_) + node0 * D, N * ROW);
+    const rsrc_t rq = make_rsrc(static_cast<const In *>(q_) + node0 * D, N * ROW);
+    constexpr int XN = F32IN ? 2 : 1;                    // 16-byte pieces per eight entries
+    uint4 kx[4][XN], qx[4][XN];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int x = 0; x < XN; ++x) {
+            const int off = l16 * ROW + (32 * s + 8 * g) * (int)sizeof(In) + 16 * x;
+            kx[s][x] = ld_u32x4<CACHED>(rk, off);
+            qx[s][x] = ld_u32x4<CACHED>(rq, off);
+        }
+    using VT = typename std::conditional<F32IN, float, unsigned short>::type;
+    VT vr[4];
+    const rsrc_t rv = make_rsrc(static_cast<const In *>(v_) + node0 * D, N * ROW);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int off = ((4 * g + r) * D + col) * (int)sizeof(In);
+        if constexpr (F32IN) vr[r] = ld_f32(rv, off);
+        else vr[r] = __builtin_amdgcn_raw_buffer_load_b16(rv, off, 0, CACHED);
+    }
+    __builtin_amdgcn_sched_barrier(0);                   // (the state's reads last: reads return in order)
+    st.load(S0, u);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- ancestors and cumulative decay by pointer jumping (see verify.hip) -----
+    float pm = l16 < N ? DecayX::mant(al) : 0.f;
+    int pe = l16 < N ? DecayX::expo(al) : 0;
+    int ptr = MODE == PREFILL ? l16 - 1 : par;
+    if (l16 >= N) ptr = -1;
+    if (ptr < -1 || ptr >= l16) {
+        if (first && lane < 16) flag_error(err, b, TREEWY_FLAG_BAD_PARENT);
+        ptr = -1;
+    }
+    int mask = ptr >= 0 ? 1 << ptr : 0;
+    while (__any(ptr >= 0)) {
+        const int src = (lane & 48) | (ptr >= 0 ? ptr : l16);
+        const float pm_s = __shfl(pm, src);
+        const int pe_s = __shfl(pe, src);
+        const int link = __shfl(mask | (ptr + 1) << 16, src);
+        if (ptr >= 0) {
+            DecayX::mul(pm, pe, pm_s, pe_s);
+            mask |= link & 0xffff;
+            ptr = (link >> 16) - 1;
+        }
+    }
+    const float inv = 1.f / pm, bt = l16 < N ? be : 0.f, gt = DecayX::value(pm, pe);
+    // ... of the nodes 4 g + r (lane group g's accumulator rows)
+    float inv4[4], g4[4], b4[4];
+    int e4[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int src = (lane & 48) | (4 * g + r);
+        inv4[r] = __shfl(inv, src);
+        e4[r] = __shfl(pe, src);
+        g4[r] = __shfl(gt, src);
+        b4[r] = __shfl(bt, src);
+    }
+
+    Keys<F32IN, F32IN ? 2 : 4> keys;
+    if constexpr (MODE == FUSED) {
+        path.check(cm, b, first, err);
+        path.template load<F32IN>(keys, 0, g, col);
+    }
+
+    // ---- gram tiles: lane t = l16, rows i = 4 g + r -------------------------------
+    bf16x8 kh[4], kl[F32IN ? 4 : 1], qh[4], ql[F32IN ? 4 : 1];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        if constexpr (F32IN) {
+            float x[8];
+            floats8(kx[s][0], kx[s][XN - 1], x);
+            split8(x, kh[s], kl[s]);
+            floats8(qx[s][0], qx[s][XN - 1], x);
+            split8(x, qh[s], ql[s]);
+        } else {
+            kh[s] = __builtin_bit_cast(bf16x8, kx[s][0]);
+            qh[s] = __builtin_bit_cast(bf16x8, qx[s][0]);
+        }
+    }
+    f32x4 gk = {}, gq = {};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        gk = mma16(kh[s], kh[s], gk);
+        gq = mma16(kh[s], qh[s], gq);
+        if constexpr (F32IN) {
+            gk = mma16(kl[s], kh[s], gk);
+            gk = mma16(kh[s], kl[s], gk);
+            gq = mma16(kl[s], qh[s], gq);
+            gq = mma16(kh[s], ql[s], gq);
+        }
+    }
+    f32x4 Bt, At;                                        // B[t][4 g + r], A[t][4 g + r]
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = 4 * g + r;
+        const bool strict = (mask >> i) & 1;
+        const float rs = DecayX::ratio(pm, pe, inv4[r], e4[r]);
+        const float ratio = strict ? rs : (i == l16 ? 1.f : 0.f);
+        Bt[r] = strict ? bt * ratio * gk[r] : 0.f;
+        float a = ratio * gq[r];
+        asm("" : "+v"(a));                               // (rounded to fp32 before it is split)
+        At[r] = a;
+    }
+    uint2 hi, lo;
+    split4(At, hi, lo);
+    const bf16x8 Ah = low8(hi), Al = low8(lo);
+
+    // ---- T, row t = l16, by the sweep; its entries 4 g + r as an operand ----------
+    bf16x8 Th, Tl;
+    {
+        float bb[16], r[16];
+        all_groups(Bt, bb);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) r[j] = bb[j];
+        sweep16<15>(r, bb, l16);
+        f32x4 t4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // (values first: a select of references goes through memory)
+            const float r0 = r[e], r1 = r[4 + e], r2 = r[8 + e], r3 = r[12 + e];
+            const float a = g & 1 ? r1 : r0, c = g & 1 ? r3 : r2;
+            t4[e] = 4 * g + e == l16 && l16 < N ? 1.f : g & 2 ? c : a;
+        }
+        split4(t4, hi, lo);
+        Th = low8(hi);
+        Tl = low8(lo);
+    }
+
+    // ---- fused: the previous round's path into the state, and the state out --------
+    if constexpr (MODE == FUSED) {
+        commit_path(st, path, keys);
+        st.store(cm.S_new, u);
+    }
+
+    // ---- P = [K; Q] S^T: lane column col, rows t = 4 g + r -------------------------
+    f32x4 pk = {}, pq = {};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        bf16x8 bh, bl;
+        if constexpr (SBF) {
+            bh = __builtin_bit_cast(bf16x8, st.x[s][0]);
+        } else {
+            float x[8];
+            floats8(st.x[s][0], st.x[s][st.SN - 1], x);
+            split8(x, bh, bl);
+        }
+        pk = mma16(kh[s], bh, pk);
+        pq = mma16(qh[s], bh, pq);
+        if constexpr (!SBF) {
+            pk = mma16(kh[s], bl, pk);
+            pq = mma16(qh[s], bl, pq);
+        }
+        if constexpr (F32IN) {
+            pk = mma16(kl[s], bh, pk);
+            pq = mma16(ql[s], bh, pq);
+        }
+    }
+    // ---- R, U = T R, O = g P_Q + A U -------------------------------------------------
+    f32x4 R;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float vt;
+        if constexpr (F32IN) vt = vr[r];
+        else vt = __builtin_bit_cast(float, (uint32_t)vr[r] << 16);
+        R[r] = b4[r] * (vt - g4[r] * pk[r]);
+        pq[r] *= g4[r];
+    }
+    auto product = [&](bf16x8 ah, bf16x8 alo, const f32x4 &x, f32x4 acc) {
+        uint2 h, l;
+        split4(x, h, l);
+        acc = mma16(ah, low8(h), acc);
+        acc = mma16(ah, low8(l), acc);
+        return mma16(alo, low8(h), acc);
+    };
+    const f32x4 uu = product(Th, Tl, R, f32x4{});
+    if constexpr (MODE != PREFILL) {
+        const rsrc_t ru = make_rsrc(U + node0 * D, N * D * 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st_f32<CACHED>(ru, ((4 * g + r) * D + col) * 4, uu[r]);
+    }
+    const f32x4 oo = product(Ah, Al, uu, pq);
+    const rsrc_t ro = make_rsrc(static_cast<In *>(o_) + node0 * D, N * ROW);
+    // (parts of a line: the default policy lets L2 merge the neighbouring waves')
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+        const int off = ((4 * g + r) * D + col) * (int)sizeof(In);
+        if constexpr (F32IN) {
+            st_f32<CACHED>(ro, off, oo[r]);
+            st_f32<CACHED>(ro, off + ROW, oo[r + 1]);
+        } else {
+            const uint32_t pr = pack_bf2(oo[r], oo[r + 1]);
+            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)pr, ro, off, 0, CACHED);
+            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(pr >> 16), ro, off + ROW, 0, CACHED);
+        }
+    }
+    if constexpr (MODE == PREFILL) {
+        // The state after the last token: g_N S + sum_l (g_N / g_l) U_l k_l^T.
+        const float mN = __shfl(pm, N - 1);
+        const int eN = __shfl(pe, N - 1);
+        const float wt = l16 < N ? DecayX::ratio(mN, eN, inv, pe) : 0.f;
+        float ua[16], x[4][8];
+        all_groups(uu, ua);
+        st.get(x, DecayX::value(mN, eN));
+        Keys<F32IN, 4> kk;
+#pragma unroll
+        for (int l0 = 0; l0 < 16; l0 += 4) {
+            if (l0 < N) {                                // (uniform; rows past the last token read zero)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) kk.load(e, rk, (l0 + e) * ROW, g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wt), l0 + e));
+                    kk.rank1(x, w * ua[l0 + e], e);
+                }
+            }
+        }
+        st.put(x);
+        st.store(cm.S_new, u);
+    }
+}
+
+// treewy_commit: the accepted path into the state, by the same waves.
+template <bool F32IN, bool SBF>
+__global__ __launch_bounds__(64 * NW) void small_commit_kernel(const void *S0, int H, int units, int32_t *__restrict__ err,
+                                                               CommitArgs cm) {
+    const int bx = blockIdx.x & 7, by = blockIdx.x >> 3;
+    const int part = by % PARTS, u = (by / PARTS) * 8 + bx;
+    if (u >= units) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    const int b = u / H, col = 16 * (part * NW + wave) + (lane & 15);
+    Path path;
+    path.issue(cm, u, b, F32IN ? 4 : 2);
+    State<SBF> st(col, g);
+    st.load(S0, u);
+    __builtin_amdgcn_sched_barrier(0);
+    path.check(cm, b, part == 0 && wave == 0, err);
+    Keys<F32IN, F32IN ? 2 : 4> keys;
+    path.template load<F32IN>(keys, 0, g, col);
+    commit_path(st, path, keys);
+    st.store(cm.S_new, u);
+}
+
+// A unit's workgroups, eight units at a time (see the kernels' unit and part).
+unsigned grid_of(int units) { return (unsigned)(((int64_t)units + 7) / 8 * 8 * PARTS); }
+
+template <bool F32IN, bool SBF, int MODE>
+hipError_t launch(const void *S0, const void *q, const void *k, const void *v, const float *alpha, const float *beta,
+                  const int32_t *parent, int N, int B, int H, void *o, float *U, int32_t *err, const CommitArgs &cm,
+                  hipStream_t stream) {
+    hipLaunchKernelGGL((small_kernel<F32IN, SBF, MODE>), dim3(grid_of(B * H)), dim3(64 * NW), 0, stream, S0, q, k, v, alpha,
+                       beta, parent, N, H, B * H, o, U, err, cm);
+    return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t dispatch(const void *S0, const void *q, const void *k, const void *v, const float *alpha, const float *beta,
+                    const int32_t *parent, int N, int B, int H, bool f32_in, bool bf16_state, void *o, float *U,
+                    int32_t *err, const CommitArgs &cm, hipStream_t stream) {
+    if (bf16_state) return launch<false, true, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
+    if (f32_in) return launch<true, false, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
+    return launch<false, false, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
+}
+
+}  // namespace
+
+// Where these kernels are used: with few units a call is one wave's chain of
+// dependent steps and a launch, and eight short waves per unit beat four long
+// ones (us a call, from a graph, this against the others'):
+//   verify of 8-node chains: 32 units 4.5 against 6.6, 128 units 5.0 against 7.5,
+//     384 units 8.5 against 11.0; of 16-node trees at 384 units 10.0 against
+//     11.3, at 512 units 12.0 both, at 1024 units 22.0 against 20.2 (K and Q come
+//     to every wave by itself);
+//   the fused call, 8-node chains: 32 units 6.6 against 10.0, 128 units 8.8
+//     against 11.1, 256 units 12.0 both; prefill of 16 tokens: 64 units 9.4
+//     against 10.4, 128 units 10.6 against 11.1, 256 units 15.6 against 12.6;
+//   commit: 32 units 4.9 against 5.3, 128 units 6.4 to 6.7 against 6.7, 256 units
+//     10.4 against 8.1 (the state's rows pass in 64-byte pieces).
+static bool few_units(int units) { return 2 * (int64_t)units <= compute_units(); }
+bool small_verify_fits(int N, int units) { return N <= 16 && 2 * (int64_t)units <= 3 * (int64_t)compute_units(); }
+bool small_commit_verify_fits(int N, int units) { return N <= 16 && few_units(units); }
+bool small_prefill_fits(int T, int units, bool f32_in) { return T <= 16 && !f32_in && few_units(units); }
+bool small_commit_fits(int N, int L_max, int units) { return N <= 64 && L_max <= 64 && few_units(units); }
+
+hipError_t launch_small_verify(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
+                               const float *beta, const int32_t *parent, int N, int B, int H, bool f32_in,
+                               bool bf16_state, void *o, float *U, int32_t *err, hipStream_t stream) {
+    return dispatch<VERIFY>(S0, q, k, v, alpha, beta, parent, N, B, H, f32_in, bf16_state, o, U, err, CommitArgs{}, stream);
+}
+
+hipError_t launch_small_commit_verify(const void *S_old, const void *q, const void *k, const void *v, const float *alpha,
+                                      const float *beta, const int32_t *parent, int N, int B, int H, bool f32_in,
+                                      bool bf16_state, void *o, float *U, int32_t *err, const CommitArgs &cm,
+                                      hipStream_t stream) {
+    return dispatch<FUSED>(S_old, q, k, v, alpha, beta, parent, N, B, H, f32_in, bf16_state, o, U, err, cm, stream);
+}
+
+hipError_t launch_small_prefill(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
+                                const float *beta, int T, int B, int H, bool bf16_state, void *S_T, void *o,
+                                hipStream_t stream) {
+    CommitArgs cm = {};
+    cm.S_new = S_T;
+    if (bf16_state)
+        return launch<false, true, PREFILL>(S0, q, k, v, alpha, beta, nullptr, T, B, H, o, nullptr, nullptr, cm, stream);
+    return launch<false, false, PREFILL>(S0, q, k, v, alpha, beta, nullptr, T, B, H, o, nullptr, nullptr, cm, stream);
+}
+
+hipError_t launch_small_commit(const void *S0, int B, int H, bool f32_k, bool bf16_state, int32_t *err,
+                               const CommitArgs &cm, hipStream_t stream) {
+    const dim3 grid(grid_of(B * H)), block(64 * NW);
+#define TREEWY_COMMIT(F, S) hipLaunchKernelGGL((small_commit_kernel<F, S>), grid, block, 0, stream, S0, H, B * H, err, cm)
+    if (f32_k) {
+        if (bf16_state) TREEWY_COMMIT(true, true);
+        else TREEWY_COMMIT(true, false);
+    } else {
+        if (bf16_state) TREEWY_COMMIT(false, true);
+        else TREEWY_COMMIT(false, false);
+    }
+#undef TREEWY_COMMIT
+    return hipGetLastError();
+}
+
+}  // namespace treewy

@@ -53,21 +53,6 @@
 
 namespace treewy {
 
-// The previous round's accepted path, committed inside verify (fused call):
-// S0 of this round = g_a S_old + sum_l w_l U_prev[a_l] k_prev[a_l]^T.
-struct CommitArgs {
-    const float *U;           // [units, N_prev, D] pseudo-values of the previous round
-    const void *k;            // [units, N_prev, D] its keys, in the input dtype
-    const float *alpha;       // [units, N_prev]
-    const int32_t *path;      // [B, L_max] root -> accepted node
-    const int32_t *path_len;  // [B]
-    const int32_t *parent;    // [B, N_prev] or null (then only range and order are checked)
-    void *S_new;              // [units, D, D] in the state dtype; may be S_old
-    int L_max, N_prev;
-    int in_stride;            // rows per unit in k and alpha (N_prev for whole tensors)
-    int u_stride;             // rows per unit in U (N_prev for whole tensors)
-};
-
 template <int NP, bool F32IN, bool FUSE = false>
 struct VerifyLds {
     static constexpr int XS = D + 8;                    // bf16 per staged K/Q row (pad breaks bank aliasing)
@@ -1583,6 +1568,8 @@ hipError_t launch_verify(const void *S0, const void *q, const void *k, const voi
                          int B, int H, bool f32_in, bool bf16_state, void *o, float *U, int32_t *err,
                          hipStream_t stream) {
     const CommitArgs none = {};
+    if (small_verify_fits(N, B * H))
+        return launch_small_verify(S0, q, k, v, alpha, beta, parent, N, B, H, f32_in, bf16_state, o, U, err, stream);
     if (N > 64) {                                        // trees of more than 64 nodes: chunks of 64
         if (bf16_state)
             return launch<64, false, false, true, TREE_CHUNKS>(S0, q, k, v, alpha, beta, parent, N, N, N, B, H, o, U,
@@ -1605,6 +1592,9 @@ hipError_t launch_commit_verify(const void *S_old, const float *U_prev, const vo
                                 void *S_new, void *o, float *U, int32_t *err, hipStream_t stream) {
     const CommitArgs cm = {U_prev, k_prev, alpha_prev, path, path_len, parent_prev, S_new, L_max, N_prev,
                            N_prev, N_prev};
+    if (small_commit_verify_fits(N, B * H))
+        return launch_small_commit_verify(S_old, q, k, v, alpha, beta, parent, N, B, H, f32_in, bf16_state, o, U, err, cm,
+                                          stream);
     return dispatch<true>(S_old, q, k, v, alpha, beta, parent, N, N, N, B, H, f32_in, bf16_state, o, U, err, cm,
                           stream);
 }

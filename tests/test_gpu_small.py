@@ -1,0 +1,134 @@
+"""The kernels of few units (drafts of at most 16 nodes, chains of at most 16
+tokens, commits), vs the float64 oracle: every wave on its own 16 columns, so
+the cases are the node counts around the four-node lane groups, chains and
+trees, each type, both sides of the unit counts where the other kernels take
+over, ragged groups of eight units, long and bad paths, and bad parents."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2608_20961_amd import workload as wl
+from tests.gpu_harness import DEV, TOL, Case, assert_close, say, units_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tw():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2608_20961_amd import treewy
+    return treewy
+
+
+def make(B, H, N, kind, dtype, seed, check=None):
+    w = wl.Workload("small", B, H, N, 128, 128, dtype, "chain" if kind == "chain" else "tree",
+                    N if kind == "chain" else min(N, 5), (1,) if kind == "chain" else (3,), (0.85, 0.999), (0.05, 0.95), 16,
+                    "uniform_node")
+    return w, Case(w, seed=seed, inputs=wl.make_inputs(w, seed=seed, cfg_key=800 + N), check_units=check)
+
+
+@pytest.mark.parametrize("dtype,state", [("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32")])
+@pytest.mark.parametrize("B,H,N,kind", [(1, 1, 1, "chain"), (2, 3, 3, "tree"), (1, 9, 4, "chain"), (2, 3, 5, "tree"),
+                                        (3, 3, 12, "chain"), (2, 4, 13, "tree"), (5, 13, 16, "chain"), (1, 3, 17, "tree"),
+                                        (2, 64, 16, "tree"), (3, 43, 9, "tree"), (6, 64, 15, "tree"), (7, 55, 16, "tree")])
+def test_round(tw, B, H, N, kind, dtype, state):
+    """verify, commit and the fused call (the committed round's draft again) of one case."""
+    say("[gpu] small %d x %d units N=%d %s %s tokens %s state" % (B, H, N, kind, dtype, state))
+    w, case = make(B, H, N, kind, dtype, 11, check=wl.sample_units(wl.Workload("s", B, H, N, 128, 128, dtype, "tree", 1, (1,),
+                                                                             (0.9, 1), (0, 1), 1, "prefix3"), 6))
+    if state == "bf16":
+        case.S0 = wl.round_to_bf16(case.S0)
+    d = case.device()
+    if state == "bf16":
+        d["S0"] = d["S0"].to(torch.bfloat16)
+    err = torch.zeros(B, dtype=torch.int32, device=DEV)
+    ver = [d[n] for n in ("q", "k", "v", "alpha", "beta", "parent")]
+    o, U = tw.treewy_verify(d["S0"], *ver, err=err)
+    S = tw.treewy_commit(d["S0"], U, d["k"], d["alpha"], d["path"], d["path_len"], parent=d["parent"], err=err)
+    S_f, o_f, U_f = tw.treewy_commit_verify(d["S0"], U, d["k"], d["alpha"], d["path"], d["path_len"], *ver,
+                                            parent_prev=d["parent"], err=err)
+    torch.cuda.synchronize()
+    assert int(err.sum()) == 0
+    o_ref, U_ref, S_ref = case.oracle()
+    tol = TOL[dtype] if state == "f32" else TOL["bf16"]
+    assert_close("o", units_of(o, w, case.check), o_ref, tol)
+    assert_close("U", units_of(U, w, case.check), U_ref, tol)
+    assert_close("S", units_of(S, w, case.check), S_ref, tol)
+    assert_close("fused S", units_of(S_f, w, case.check), S_ref, tol)
+    c = case.check
+    par = np.repeat(case.x["parent"], w.H, axis=0)[c]
+    S_in = units_of(S_f, w, c)                           # (verified from the state as written)
+    o2, U2 = oracle.verify(S_in, case.unit_view("q"), case.unit_view("k"), case.unit_view("v"), case.unit_view("alpha"),
+                           case.unit_view("beta"), par)
+    assert_close("fused o", units_of(o_f, w, c), o2, tol)
+    assert_close("fused U", units_of(U_f, w, c), U2, tol)
+
+
+@pytest.mark.parametrize("state", ["f32", "bf16"])
+@pytest.mark.parametrize("units,T", [((1, 1), 1), ((2, 3), 4), ((1, 9), 13), ((2, 64), 16), ((3, 43), 16)])
+def test_prefill(tw, units, T, state):
+    B, H = units
+    say("[gpu] small prefill %d x %d units T=%d %s state" % (B, H, T, state))
+    w, case = make(B, H, T, "chain", "bf16", 12)
+    S0 = wl.round_to_bf16(case.S0) if state == "bf16" else case.S0
+    d = case.device()
+    S0_d = torch.from_numpy(S0.reshape(B, H, 128, 128)).to(DEV).to(torch.bfloat16 if state == "bf16" else torch.float32)
+    S_T, o = tw.treewy_chain_prefill(S0_d, d["q"], d["k"], d["v"], d["alpha"], d["beta"])
+    in_place = S0_d.clone()
+    tw.treewy_chain_prefill(in_place, d["q"], d["k"], d["v"], d["alpha"], d["beta"], S_T=in_place)
+    torch.cuda.synchronize()
+    assert torch.equal(in_place, S_T)
+    args = [case.unit_view(n) for n in ("k", "v", "alpha", "beta")]
+    S_ref = oracle.chain(S0, *args)
+    o_ref, _ = oracle.verify(S0, case.unit_view("q"), *args, np.tile(np.arange(-1, T - 1, dtype=np.int32), (w.units, 1)))
+    assert_close("S_T", units_of(S_T, w, case.check), S_ref, TOL["bf16"])
+    assert_close("o", units_of(o, w, case.check), o_ref, TOL["bf16"])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("L", [0, 1, 3, 4, 5, 16, 63, 64])
+def test_commit_path_lengths(tw, L, dtype):
+    """Paths in batches of four (two with fp32 keys) of a 64-node chain, into the commit and the fused call."""
+    w, case = make(2, 3, 64, "chain", dtype, 13)
+    case.x["path"] = np.tile(np.arange(64, dtype=np.int32), (2, 1))
+    case.x["path_len"] = np.full(2, L, dtype=np.int32)
+    d = case.device()
+    _, U = tw.treewy_verify(d["S0"], *[d[n] for n in ("q", "k", "v", "alpha", "beta", "parent")])
+    S = tw.treewy_commit(d["S0"], U, d["k"], d["alpha"], d["path"], d["path_len"])
+    now = [d[n][:, :, :5].contiguous() for n in ("q", "k", "v", "alpha", "beta")]
+    S_f, _, _ = tw.treewy_commit_verify(d["S0"], U, d["k"], d["alpha"], d["path"], d["path_len"], *now,
+                                        d["parent"][:, :5].contiguous(), parent_prev=d["parent"])
+    torch.cuda.synchronize()
+    _, _, S_ref = case.oracle()
+    assert_close("S", units_of(S, w, case.check), S_ref, TOL[dtype])
+    assert_close("fused S", units_of(S_f, w, case.check), S_ref, TOL[dtype])
+    if L == 0:
+        assert torch.equal(S, d["S0"]) and torch.equal(S_f, d["S0"])
+
+
+def test_malformed(tw):
+    """A bad parent counts as -1, a bad path keeps the state, each with its flag and only for its sequence."""
+    w, case = make(3, 2, 9, "chain", "bf16", 14)
+    par = case.x["parent"].copy()
+    par[1, 4], par[1, 7] = 4, -3
+    case.x["parent"][1, 4] = case.x["parent"][1, 7] = -1
+    case.x["path_len"][:] = 0
+    d = case.device()
+    err = torch.zeros(3, dtype=torch.int32, device=DEV)
+    o, U = tw.treewy_verify(d["S0"], *[d[n] for n in ("q", "k", "v", "alpha", "beta")], torch.from_numpy(par).to(DEV), err=err)
+    torch.cuda.synchronize()
+    assert err.tolist() == [0, 1, 0]
+    o_ref, U_ref, _ = case.oracle()
+    assert_close("o", units_of(o, w, case.check), o_ref, TOL["bf16"])
+    assert_close("U", units_of(U, w, case.check), U_ref, TOL["bf16"])
+    path = torch.tensor([[0, 1, 2], [0, 2, 1], [0, 1, 9]], dtype=torch.int32, device=DEV)
+    for plen, flags in (([3, 3, 3], [0, 2, 2]), ([3, 2, 2], [0, 0, 0]), ([4, -1, 0], [2, 2, 0])):
+        err.zero_()
+        S = tw.treewy_commit(d["S0"], U, d["k"], d["alpha"], path, torch.tensor(plen, dtype=torch.int32, device=DEV), err=err)
+        torch.cuda.synchronize()
+        assert err.tolist() == flags
+        for b in range(3):
+            if flags[b]:
+                assert torch.equal(S[b], d["S0"][b])
