@@ -45,8 +45,8 @@ inline int compute_units() {
 }
 
 // The kernels of few units (small.hip), and for which sizes they are used.
-bool small_verify_fits(int N, int units);
-bool small_commit_verify_fits(int N, int units);
+bool small_verify_fits(int N, int units, bool f32_in);
+bool small_commit_verify_fits(int N, int units, bool f32_in);
 bool small_prefill_fits(int T, int units, bool f32_in);
 bool small_commit_fits(int N, int L_max, int units);
 hipError_t launch_small_verify(const void *S0, const void *q, const void *k, const void *v, const float *alpha,

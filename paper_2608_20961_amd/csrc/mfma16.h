@@ -25,6 +25,20 @@ __device__ __forceinline__ void split4(f32x4 x, uint2 &hi, uint2 &lo) {
 // Four contraction entries of a lane group as the low half of its eight slots, the others empty.
 __device__ __forceinline__ bf16x8 low8(uint2 x) { return __builtin_bit_cast(bf16x8, make_uint4(x.x, x.y, 0u, 0u)); }
 
+// Operand of a transposed LDS read: within each 16 lanes, lane 4 j + y points at
+// four 16-bit entries of row j and lane i receives column i of the 4 x 16 block.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
+
+// A bijection of t % 16 onto the 16 granules of a row, which sends four
+// consecutive rows to four different groups of four granules.
+__device__ __forceinline__ int swz(int t) { return ((t & 3) << 2) | ((t >> 2) & 3); }
+
+// LDS written and read again by the same wave: the hardware keeps a wave's
+// LDS accesses in order; this keeps the compiler from reordering accesses of
+// different types.
+__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
 // r[j] += x * (b[j] of lane I of each row of 16 lanes), j = 0 .. NJ - 1: the row
 // broadcast rides on the multiply-add (the compiler leaves it a move of its
 // own).  (A DPP source must have been written two wait states before: s_nop.)

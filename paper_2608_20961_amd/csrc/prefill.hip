@@ -64,15 +64,6 @@ struct Slot {
     static_assert(T_OFF % 16 == 0 && A_OFF % 16 == 0 && G_OFF % 16 == 0 && BYTES % 16 == 0, "alignment");
 };
 
-// A bijection of t % 16 onto the 16 granules of a row, which sends four
-// consecutive rows to four different groups of four granules.
-__device__ __forceinline__ int swz(int t) { return ((t & 3) << 2) | ((t >> 2) & 3); }
-
-// LDS written and read again by the same wave: the hardware keeps a wave's
-// LDS accesses in order; this keeps the compiler from reordering accesses of
-// different types.
-__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
-
 // Waves of a workgroup by role.  Waves go round the CU's four SIMDs; with two
 // state waves the workgroup is launched with eight, of which waves 4 and 5
 // end at once, so that each state wave has a SIMD to itself and the chunk
@@ -254,8 +245,6 @@ __global__ __launch_bounds__(64 * launched_waves<NS>(PW), (launched_waves<NS>(PW
                 for (int e = 0; e < 4; ++e) x8[4 * m + e] = uu[m][e] * w4[e];
             }
             split8(x8, wh, wl);
-            typedef short s16x4 __attribute__((ext_vector_type(4)));
-            typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
             auto kt = [&](int off, int jt) {             // rows d_k 16 jt + l16 of K^T at tokens 16 h + 4 g + r
                 s16x4 a[2];
 #pragma unroll
@@ -488,8 +477,6 @@ __global__ __launch_bounds__(64 * launched_waves<NS>(PW), (launched_waves<NS>(PW
                 if (lane < n) *reinterpret_cast<unsigned short *>(th + (lane * L::TS + pos32(lane)) * 2) = 0x3F80;   // 1 on the diagonal
                 lds_order();
                 // Rows 4 g + e of T0, column tl (a transposed read), and of T1, row tl.
-                typedef short s16x4 __attribute__((ext_vector_type(4)));
-                typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
                 const unsigned char *t0 = th + (4 * g + (tl >> 2)) * L::TS * 2 + 16 * (tl & 3);
                 const unsigned char *t1 = th + ((16 + tl) * L::TS + 8 * g + 4) * 2;
                 const bf16x8 t0h = low8(__builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)t0)));

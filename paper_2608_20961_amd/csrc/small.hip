@@ -1,5 +1,5 @@
-// Few units: drafts of at most 16 nodes (treewy_verify, treewy_commit_verify),
-// chains of at most 16 tokens (treewy_chain_prefill) and treewy_commit: the system
+// Few units: drafts of at most 48 nodes (treewy_verify, treewy_commit_verify),
+// chains of at most 32 tokens (treewy_chain_prefill) and treewy_commit: the system
 // of verify.hip on 16-row tiles, every wave on its own.  Bound by the latency of
 // the wave's reads and of its steps.
 //
@@ -258,8 +258,7 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
     const size_t node0 = (size_t)u * N;
 
     // ---- every read of the wave, in the order it needs them -------------------
-    int par = 0;
-    if constexpr (MODE != PREFILL) par = ld_i32(make_rsrc(parent + (size_t)b * N, N * 4), l16 * 4);
+    const int par = ld_i32(make_rsrc(parent + (size_t)b * N, N * 4), l16 * 4);
     const float al = ld_f32(make_rsrc(alpha + node0, N * 4), l16 * 4);
     const float be = ld_f32(make_rsrc(beta + node0, N * 4), l16 * 4);
     Path path;
@@ -292,8 +291,7 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
     // ---- ancestors and cumulative decay by pointer jumping (see verify.hip) -----
     float pm = l16 < N ? DecayX::mant(al) : 0.f;
     int pe = l16 < N ? DecayX::expo(al) : 0;
-    int ptr = MODE == PREFILL ? l16 - 1 : par;
-    if (l16 >= N) ptr = -1;
+    int ptr = l16 < N ? par : -1;
     if (ptr < -1 || ptr >= l16) {
         if (first && lane < 16) flag_error(err, b, TREEWY_FLAG_BAD_PARENT);
         ptr = -1;
@@ -440,11 +438,9 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
         return mma16(alo, low8(h), acc);
     };
     const f32x4 uu = product(Th, Tl, R, f32x4{});
-    if constexpr (MODE != PREFILL) {
-        const rsrc_t ru = make_rsrc(U + node0 * D, N * D * 4);
+    const rsrc_t ru = make_rsrc(U + node0 * D, N * D * 4);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) st_f32<CACHED>(ru, ((4 * g + r) * D + col) * 4, uu[r]);
-    }
+    for (int r = 0; r < 4; ++r) st_f32<CACHED>(ru, ((4 * g + r) * D + col) * 4, uu[r]);
     const f32x4 oo = product(Ah, Al, uu, pq);
     const rsrc_t ro = make_rsrc(static_cast<In *>(o_) + node0 * D, N * ROW);
     // (parts of a line: the default policy lets L2 merge the neighbouring waves')
@@ -460,27 +456,334 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
             __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(pr >> 16), ro, off + ROW, 0, CACHED);
         }
     }
-    if constexpr (MODE == PREFILL) {
-        // The state after the last token: g_N S + sum_l (g_N / g_l) U_l k_l^T.
-        const float mN = __shfl(pm, N - 1);
-        const int eN = __shfl(pe, N - 1);
-        const float wt = l16 < N ? DecayX::ratio(mN, eN, inv, pe) : 0.f;
-        float ua[16], x[4][8];
-        all_groups(uu, ua);
-        st.get(x, DecayX::value(mN, eN));
-        Keys<F32IN, 4> kk;
+}
+
+// x_j of lane group i <-> x_i of lane group j (a 4 x 4 transpose between the four values and the four lane groups).
+__device__ __forceinline__ void transpose_groups(float (&x)[4]) {
+    int v[4];
 #pragma unroll
-        for (int l0 = 0; l0 < 16; l0 += 4) {
-            if (l0 < N) {                                // (uniform; rows past the last token read zero)
+    for (int j = 0; j < 4; ++j) {
+        const float f = x[j];
+        v[j] = __builtin_bit_cast(int, f);
+    }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) kk.load(e, rk, (l0 + e) * ROW, g);
+    for (int j = 0; j < 4; j += 2) {
+        const auto p = __builtin_amdgcn_permlane16_swap(v[j], v[j + 1], false, false);
+        v[j] = p[0];
+        v[j + 1] = p[1];
+    }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wt), l0 + e));
-                    kk.rank1(x, w * ua[l0 + e], e);
-                }
+    for (int j = 0; j < 2; ++j) {
+        const auto p = __builtin_amdgcn_permlane32_swap(v[j], v[j + 2], false, false);
+        v[j] = p[0];
+        v[j + 2] = p[1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int i = v[j];
+        x[j] = __builtin_bit_cast(float, i);
+    }
+}
+
+// Drafts of up to 16 NT nodes of bf16 tokens, the same way: NT tiles of 16 nodes.
+// In the walk lane = node; its results go through a piece of LDS that belongs
+// to the wave.  The diagonal blocks of T are swept at once, block q in lane group
+// q (a transpose across the lane groups before and after turns the gram's
+// layout into rows and back); T itself is not formed: U comes by forward
+// substitution over the tiles, U_a = T_a (R_a - sum over b < a of B_ab U_b), whose
+// operands B_ab and A_ab are the gram tiles as the accumulators hold them.
+template <bool SBF, int MODE, int NT>
+__global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void tiles_kernel(
+    const void *S0, const void *__restrict__ q_, const void *__restrict__ k_, const void *__restrict__ v_,
+    const float *__restrict__ alpha, const float *__restrict__ beta, const int32_t *__restrict__ parent, int N, int H,
+    int units, void *__restrict__ o_, float *U, int32_t *__restrict__ err, CommitArgs cm) {
+    using In = __bf16;
+    static_assert(NT == 2 || NT == 3, "at most 48 nodes: with four tiles what every wave repeats outweighs what it saves");
+    constexpr int ROW = D * (int)sizeof(In);
+    constexpr int N_INV = 0, N_EXP = 1, N_GVAL = 2, N_BETA = 3, N_MANT = 4, N_MASK0 = 5, N_MASK1 = 6, FIELDS = 7;
+    __shared__ __attribute__((aligned(16))) int node_s[NW][FIELDS][64];
+    __shared__ __attribute__((aligned(16))) unsigned char k_s[MODE == PREFILL ? NW : 1][MODE == PREFILL ? 32 * 256 : 16];
+    const int bx = blockIdx.x & 7, by = blockIdx.x >> 3;
+    const int part = by % PARTS, u = (by / PARTS) * 8 + bx;
+    if (u >= units) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+    const int b = u / H, col = 16 * (part * NW + wave) + l16;
+    State<SBF> st(col, g);
+    const bool first = part == 0 && wave == 0;
+    const size_t node0 = (size_t)u * N;
+
+    // ---- every read of the wave, in the order it needs them -------------------
+    int par = lane - 1;                                  // (a chain)
+    if constexpr (MODE != PREFILL) par = ld_i32(make_rsrc(parent + (size_t)b * N, N * 4), lane * 4);
+    const float al = ld_f32(make_rsrc(alpha + node0, N * 4), lane * 4);
+    const float be = ld_f32(make_rsrc(beta + node0, N * 4), lane * 4);
+    Path path;
+    if constexpr (MODE == FUSED) path.issue(cm, u, b, sizeof(In));
+    const rsrc_t rk = make_rsrc(static_cast<const In *>(k_) + node0 * D, N * ROW);
+    const rsrc_t rq = make_rsrc(static_cast<const In *>(q_) + node0 * D, N * ROW);
+    bf16x8 kh[NT][4], qh[NT][4];
+    auto load_rows = [&](bf16x8 (&x)[NT][4], rsrc_t r) {
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                x[a][s] = __builtin_bit_cast(bf16x8, ld_u32x4<CACHED>(r, (16 * a + l16) * ROW + (32 * s + 8 * g) * 2));
+    };
+    load_rows(kh, rk);
+    load_rows(qh, rq);
+    unsigned short vr[NT][4];
+    const rsrc_t rv = make_rsrc(static_cast<const In *>(v_) + node0 * D, N * ROW);
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            vr[a][r] = __builtin_amdgcn_raw_buffer_load_b16(rv, ((16 * a + 4 * g + r) * D + col) * 2, 0, CACHED);
+    __builtin_amdgcn_sched_barrier(0);
+    st.load(S0, u);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- ancestors and cumulative decay by pointer jumping (lane = node) --------
+    float wt = 0.f, gN = 0.f;                            // prefill: the update's weight of token = lane, and g_N
+    {
+        float pm = lane < N ? DecayX::mant(al) : 0.f;
+        int pe = lane < N ? DecayX::expo(al) : 0;
+        int ptr = lane < N ? par : -1;
+        if (ptr < -1 || ptr >= lane) {
+            if (first) flag_error(err, b, TREEWY_FLAG_BAD_PARENT);
+            ptr = -1;
+        }
+        int m0 = ptr >= 0 && ptr < 32 ? 1 << ptr : 0, m1 = ptr >= 32 ? 1 << (ptr - 32) : 0;
+        while (__any(ptr >= 0)) {
+            const int src = ptr >= 0 ? ptr : lane;
+            const float pm_s = __shfl(pm, src);
+            const int pe_s = __shfl(pe, src), ptr_s = __shfl(ptr, src), m0_s = __shfl(m0, src);
+            const int m1_s = NT > 2 ? __shfl(m1, src) : 0;
+            if (ptr >= 0) {
+                DecayX::mul(pm, pe, pm_s, pe_s);
+                m0 |= m0_s;
+                m1 |= m1_s;
+                ptr = ptr_s;
             }
         }
+        const float inv = 1.f / pm, bt = lane < N ? be : 0.f, gt = DecayX::value(pm, pe);
+        if constexpr (MODE == PREFILL) {
+            const float mN = __shfl(pm, N - 1);
+            const int eN = __shfl(pe, N - 1);
+            wt = lane < N ? DecayX::ratio(mN, eN, inv, pe) : 0.f;
+            gN = DecayX::value(mN, eN);
+        }
+        int(&w)[FIELDS][64] = node_s[wave];
+        w[N_INV][lane] = __builtin_bit_cast(int, inv);
+        w[N_EXP][lane] = pe;
+        w[N_GVAL][lane] = __builtin_bit_cast(int, gt);
+        w[N_BETA][lane] = __builtin_bit_cast(int, bt);
+        w[N_MANT][lane] = __builtin_bit_cast(int, pm);
+        w[N_MASK0][lane] = m0;
+        w[N_MASK1][lane] = m1;
+    }
+    lds_order();
+    auto field1 = [&](int f, int a) { return node_s[wave][f][16 * a + l16]; };
+    auto field4 = [&](int f, int a) { return *reinterpret_cast<const int4 *>(&node_s[wave][f][16 * a + 4 * g]); };
+    Keys<false, 4> keys;
+    if constexpr (MODE == FUSED) {
+        path.check(cm, b, first, err);
+        path.template load<false>(keys, 0, g, col);
+    }
+
+    // ---- gram tiles: lane t = 16 a + l16, rows i = 16 bb + 4 g + r, bb <= a --------
+    constexpr int PAIRS = NT * (NT + 1) / 2;             // tile (a, bb) at a (a + 1) / 2 + bb
+    uint2 Bh[PAIRS], Bl[PAIRS], Ah[PAIRS], Al[PAIRS];    // -B off the diagonal, and A, as operands
+    float Bd[4][4] = {};                                 // B's diagonal tiles
+#pragma unroll
+    for (int a = 0; a < NT; ++a) {
+        const float mt = __builtin_bit_cast(float, field1(N_MANT, a)), bt = __builtin_bit_cast(float, field1(N_BETA, a));
+        const int et = field1(N_EXP, a), m0 = field1(N_MASK0, a), m1 = NT > 2 ? field1(N_MASK1, a) : 0;
+#pragma unroll
+        for (int bb = 0; bb <= a; ++bb) {
+            f32x4 gk = {}, gq = {};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                gk = mma16(kh[bb][s], kh[a][s], gk);
+                gq = mma16(kh[bb][s], qh[a][s], gq);
+            }
+            const int4 iv = field4(N_INV, bb), ev = field4(N_EXP, bb);
+            const int i4[4] = {iv.x, iv.y, iv.z, iv.w}, e4[4] = {ev.x, ev.y, ev.z, ev.w};
+            const int bits = (bb < 2 ? m0 : m1) >> (16 * (bb & 1) + 4 * g);
+            const int p = a * (a + 1) / 2 + bb;
+            f32x4 Bt, At;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int iv_r = i4[r];
+                const bool strict = (bits >> r) & 1, self = a == bb && 4 * g + r == l16;
+                const float rs = DecayX::ratio(mt, et, __builtin_bit_cast(float, iv_r), e4[r]);
+                const float ratio = strict ? rs : self ? 1.f : 0.f;
+                Bt[r] = strict ? bt * ratio * gk[r] : 0.f;
+                float x = ratio * gq[r];
+                asm("" : "+v"(x));                       // (rounded to fp32 before it is split)
+                At[r] = x;
+            }
+            split4(At, Ah[p], Al[p]);
+            if (a == bb) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) Bd[a][r] = Bt[r];
+            } else {
+                split4(-Bt, Bh[p], Bl[p]);
+            }
+        }
+    }
+
+    // ---- the diagonal blocks of T: block q's rows in lane group q ------------------
+    uint2 Th[4], Tl[4];
+    {
+        float bb[16], r[16];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float x[4] = {Bd[0][e], Bd[1][e], Bd[2][e], Bd[3][e]};
+            transpose_groups(x);                         // group q: its row's entries 4 j + e
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[4 * j + e] = bb[4 * j + e] = x[j];
+        }
+        sweep16<15>(r, bb, l16);
+        f32x4 t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float f = r[4 * j + e];
+                x[j] = 4 * j + e == l16 && lane < N ? 1.f : f;
+            }
+            transpose_groups(x);                         // group g: block q's entries 4 g + e
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q][e] = x[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NT; ++q) split4(t[q], Th[q], Tl[q]);
+    }
+
+    // ---- fused: the previous round's path into the state, and the state out --------
+    if constexpr (MODE == FUSED) {
+        commit_path(st, path, keys);
+        st.store(cm.S_new, u);
+    }
+
+    // ---- P = [K; Q] S^T: lane column col, rows 16 a + 4 g + r -----------------------
+    f32x4 pk[NT] = {}, pq[NT] = {};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        bf16x8 bh, bl;
+        if constexpr (SBF) {
+            bh = __builtin_bit_cast(bf16x8, st.x[s][0]);
+        } else {
+            float x[8];
+            floats8(st.x[s][0], st.x[s][st.SN - 1], x);
+            split8(x, bh, bl);
+        }
+#pragma unroll
+        for (int a = 0; a < NT; ++a) {
+            pk[a] = mma16(kh[a][s], bh, pk[a]);
+            pq[a] = mma16(qh[a][s], bh, pq[a]);
+        }
+        if constexpr (!SBF) {
+#pragma unroll
+            for (int a = 0; a < NT; ++a) {
+                pk[a] = mma16(kh[a][s], bl, pk[a]);
+                pq[a] = mma16(qh[a][s], bl, pq[a]);
+            }
+        }
+    }
+    // ---- R, then tile by tile U_a = T_a (R_a - sum B_ab U_b) and O_a = g P_Q + sum A_ab U_b
+    auto product = [&](uint2 ah, uint2 alo, uint2 xh, uint2 xl, f32x4 acc) {
+        acc = mma16(low8(ah), low8(xh), acc);
+        acc = mma16(low8(ah), low8(xl), acc);
+        return mma16(low8(alo), low8(xh), acc);
+    };
+    const rsrc_t ru = make_rsrc(MODE == PREFILL ? nullptr : U + node0 * D, MODE == PREFILL ? 0 : N * D * 4);
+    const rsrc_t ro = make_rsrc(static_cast<In *>(o_) + node0 * D, N * ROW);
+    uint2 uh[NT], ul[NT];
+    f32x4 u32[MODE == PREFILL ? NT : 1];
+#pragma unroll
+    for (int a = 0; a < NT; ++a) {
+        const int4 gv = field4(N_GVAL, a), bv = field4(N_BETA, a);
+        const int g4[4] = {gv.x, gv.y, gv.z, gv.w}, b4[4] = {bv.x, bv.y, bv.z, bv.w};
+        f32x4 R;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float vt = __builtin_bit_cast(float, (uint32_t)vr[a][r] << 16);
+            const int gi = g4[r], bi = b4[r];
+            const float gr = __builtin_bit_cast(float, gi), br = __builtin_bit_cast(float, bi);
+            R[r] = br * (vt - gr * pk[a][r]);
+            pq[a][r] *= gr;
+        }
+#pragma unroll
+        for (int bb = 0; bb < a; ++bb) R = product(Bh[a * (a + 1) / 2 + bb], Bl[a * (a + 1) / 2 + bb], uh[bb], ul[bb], R);
+        uint2 rh, rl;
+        split4(R, rh, rl);
+        const f32x4 uu = product(Th[a], Tl[a], rh, rl, f32x4{});
+        if constexpr (MODE == PREFILL) u32[a] = uu;
+        else
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st_f32<CACHED>(ru, ((16 * a + 4 * g + r) * D + col) * 4, uu[r]);
+        split4(uu, uh[a], ul[a]);
+        f32x4 oo = pq[a];
+#pragma unroll
+        for (int bb = 0; bb <= a; ++bb) oo = product(Ah[a * (a + 1) / 2 + bb], Al[a * (a + 1) / 2 + bb], uh[bb], ul[bb], oo);
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+            const int off = ((16 * a + 4 * g + r) * D + col) * (int)sizeof(In);
+            const uint32_t pr = pack_bf2(oo[r], oo[r + 1]);
+            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)pr, ro, off, 0, CACHED);
+            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(pr >> 16), ro, off + ROW, 0, CACHED);
+        }
+    }
+    if constexpr (MODE == PREFILL) {
+        node_s[wave][N_INV][lane] = __builtin_bit_cast(int, wt);
+        float x[4][8];
+        st.get(x, gN);
+        // The update K^T (w U) on the matrix cores: K's rows through LDS of the
+        // wave's own for the transposed reads (granule G of 16 bytes of row t at G ^
+        // swz(t)), w U as the accumulators hold it.  Slots e < 4 of lane group g are
+        // token 4 g + e, the others token 16 + 4 g + e - 4; row 4 y + r of product
+        // (s, h) is d_k 32 s + 8 y + 4 h + r, so its rows 4 g + r land on this
+        // lane's entries.
+        static_assert(MODE != PREFILL || NT == 2, "32 tokens: one step of the contraction");
+        unsigned char *ks = k_s[wave];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                *reinterpret_cast<bf16x8 *>(ks + (16 * a + l16) * 256 + (((4 * s + g) ^ swz(l16)) << 4)) = kh[a][s];
+        lds_order();
+        float wu[8];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const int4 wv = field4(N_INV, a);            // (the weights by now)
+            const int w4[4] = {wv.x, wv.y, wv.z, wv.w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int wi = w4[r];
+                wu[4 * a + r] = __builtin_bit_cast(float, wi) * u32[a][r];
+            }
+        }
+        bf16x8 wh, wl;
+        split8(wu, wh, wl);
+        const int j4 = l16 >> 2, y = l16 & 3;
+        const int tr_addr = (4 * g + j4) * 256 + ((y ^ swz(4 * g + j4)) << 4);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const unsigned char *at = ks + 8 * h + (tr_addr ^ (s << 6));
+                const s16x4 k0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
+                const s16x4 k1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at + 16 * 256));
+                const bf16x8 kt = __builtin_bit_cast(bf16x8, __builtin_shufflevector(k0, k1, 0, 1, 2, 3, 4, 5, 6, 7));
+                f32x4 d = {x[s][4 * h], x[s][4 * h + 1], x[s][4 * h + 2], x[s][4 * h + 3]};
+                d = mma16(kt, wh, d);
+                d = mma16(kt, wl, d);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[s][4 * h + r] = d[r];
+            }
         st.put(x);
         st.store(cm.S_new, u);
     }
@@ -520,33 +823,65 @@ hipError_t launch(const void *S0, const void *q, const void *k, const void *v, c
     return hipGetLastError();
 }
 
+template <bool SBF, int MODE, int NT>
+hipError_t launch_tiles(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
+                        const float *beta, const int32_t *parent, int N, int B, int H, void *o, float *U, int32_t *err,
+                        const CommitArgs &cm, hipStream_t stream) {
+    hipLaunchKernelGGL((tiles_kernel<SBF, MODE, NT>), dim3(grid_of(B * H)), dim3(64 * NW), 0, stream, S0, q, k, v, alpha,
+                       beta, parent, N, H, B * H, o, U, err, cm);
+    return hipGetLastError();
+}
+
 template <int MODE>
 hipError_t dispatch(const void *S0, const void *q, const void *k, const void *v, const float *alpha, const float *beta,
                     const int32_t *parent, int N, int B, int H, bool f32_in, bool bf16_state, void *o, float *U,
                     int32_t *err, const CommitArgs &cm, hipStream_t stream) {
-    if (bf16_state) return launch<false, true, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
-    if (f32_in) return launch<true, false, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
-    return launch<false, false, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
+#define TREEWY_TILES(S, NT)                                                                                          \
+    launch_tiles<S, MODE, NT>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream)
+    if constexpr (MODE == PREFILL) {
+        return bf16_state ? TREEWY_TILES(true, 2) : TREEWY_TILES(false, 2);
+    } else {
+        if (N > 16) {                                    // (bf16 tokens: see tiles_fit)
+            if (bf16_state) return N <= 32 ? TREEWY_TILES(true, 2) : TREEWY_TILES(true, 3);
+            return N <= 32 ? TREEWY_TILES(false, 2) : TREEWY_TILES(false, 3);
+        }
+        if (bf16_state) return launch<false, true, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
+        if (f32_in) return launch<true, false, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
+        return launch<false, false, MODE>(S0, q, k, v, alpha, beta, parent, N, B, H, o, U, err, cm, stream);
+    }
+#undef TREEWY_TILES
 }
 
 }  // namespace
 
 // Where these kernels are used: with few units a call is one wave's chain of
 // dependent steps and a launch, and eight short waves per unit beat four long
-// ones (us a call, from a graph, this against the others'):
-//   verify of 8-node chains: 32 units 4.5 against 6.6, 128 units 5.0 against 7.5,
-//     384 units 8.5 against 11.0; of 16-node trees at 384 units 10.0 against
-//     11.3, at 512 units 12.0 both, at 1024 units 22.0 against 20.2 (K and Q come
-//     to every wave by itself);
-//   the fused call, 8-node chains: 32 units 6.6 against 10.0, 128 units 8.8
-//     against 11.1, 256 units 12.0 both; prefill of 16 tokens: 64 units 9.4
-//     against 10.4, 128 units 10.6 against 11.1, 256 units 15.6 against 12.6;
+// ones; with many, what every wave repeats (K and Q, the gram, the solve) costs
+// more.  us a call, from a graph, this against the others':
+//   verify, at most 16 nodes: 8-node chains in 32 units 4.5 against 6.6, 128 units
+//     5.0 against 7.5, 384 units 8.5 against 11.0; 16-node trees in 384 units 10.0
+//     against 11.3, 512 units 12.0 both, 1024 units 22.0 against 20.2;
+//   verify, more nodes, bf16 tokens: 32 nodes in 64 units 6.6 against 7.2, 128 units
+//     7.0 against 7.8, 192 units 10.7 against 8.1; 39 and 48 nodes in 128 units 8.1
+//     and 9.0 against 9.9 and 11.1, 192 units 11.6 and 13.9 against 10.3 and 11.7; 64
+//     nodes in four tiles 11.2 against 10.6 already at 64 units, 24 nodes with fp32
+//     tokens 8.7 against 8.5;
+//   the fused call: 8-node chains in 32 units 6.6 against 10.0, 128 units 8.8 against
+//     11.1, 256 units 12.0 both; 32 nodes in 128 units 10.7 against 11.2, 192 units
+//     15.7 against 12.0;
+//   prefill of 20 tokens: 64 units 8.2 against 10.3, 128 units 9.2 against 10.9, 192
+//     units 11.7 against 11.3;
 //   commit: 32 units 4.9 against 5.3, 128 units 6.4 to 6.7 against 6.7, 256 units
 //     10.4 against 8.1 (the state's rows pass in 64-byte pieces).
 static bool few_units(int units) { return 2 * (int64_t)units <= compute_units(); }
-bool small_verify_fits(int N, int units) { return N <= 16 && 2 * (int64_t)units <= 3 * (int64_t)compute_units(); }
-bool small_commit_verify_fits(int N, int units) { return N <= 16 && few_units(units); }
-bool small_prefill_fits(int T, int units, bool f32_in) { return T <= 16 && !f32_in && few_units(units); }
+static bool tiles_fit(int N, int units, bool f32_in) { return N > 16 && N <= 48 && !f32_in && few_units(units); }
+bool small_verify_fits(int N, int units, bool f32_in) {
+    return (N <= 16 && 2 * (int64_t)units <= 3 * (int64_t)compute_units()) || tiles_fit(N, units, f32_in);
+}
+bool small_commit_verify_fits(int N, int units, bool f32_in) {
+    return (N <= 16 && few_units(units)) || tiles_fit(N, units, f32_in);
+}
+bool small_prefill_fits(int T, int units, bool f32_in) { return T <= 32 && !f32_in && few_units(units); }
 bool small_commit_fits(int N, int L_max, int units) { return N <= 64 && L_max <= 64 && few_units(units); }
 
 hipError_t launch_small_verify(const void *S0, const void *q, const void *k, const void *v, const float *alpha,
@@ -567,9 +902,7 @@ hipError_t launch_small_prefill(const void *S0, const void *q, const void *k, co
                                 hipStream_t stream) {
     CommitArgs cm = {};
     cm.S_new = S_T;
-    if (bf16_state)
-        return launch<false, true, PREFILL>(S0, q, k, v, alpha, beta, nullptr, T, B, H, o, nullptr, nullptr, cm, stream);
-    return launch<false, false, PREFILL>(S0, q, k, v, alpha, beta, nullptr, T, B, H, o, nullptr, nullptr, cm, stream);
+    return dispatch<PREFILL>(S0, q, k, v, alpha, beta, nullptr, T, B, H, false, bf16_state, o, nullptr, nullptr, cm, stream);
 }
 
 hipError_t launch_small_commit(const void *S0, int B, int H, bool f32_k, bool bf16_state, int32_t *err,

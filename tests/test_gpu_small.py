@@ -1,8 +1,9 @@
-"""The kernels of few units (drafts of at most 16 nodes, chains of at most 16
+"""The kernels of few units (drafts of at most 48 nodes, chains of at most 32
 tokens, commits), vs the float64 oracle: every wave on its own 16 columns, so
-the cases are the node counts around the four-node lane groups, chains and
-trees, each type, both sides of the unit counts where the other kernels take
-over, ragged groups of eight units, long and bad paths, and bad parents."""
+the cases are the node counts around the four-node lane groups and the 16-node
+tiles, chains and trees, each type, both sides of the unit counts where the
+other kernels take over, ragged groups of eight units, long and bad paths, and
+bad parents."""
 import numpy as np
 import pytest
 import torch
@@ -32,7 +33,9 @@ def make(B, H, N, kind, dtype, seed, check=None):
 @pytest.mark.parametrize("dtype,state", [("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32")])
 @pytest.mark.parametrize("B,H,N,kind", [(1, 1, 1, "chain"), (2, 3, 3, "tree"), (1, 9, 4, "chain"), (2, 3, 5, "tree"),
                                         (3, 3, 12, "chain"), (2, 4, 13, "tree"), (5, 13, 16, "chain"), (1, 3, 17, "tree"),
-                                        (2, 64, 16, "tree"), (3, 43, 9, "tree"), (6, 64, 15, "tree"), (7, 55, 16, "tree")])
+                                        (2, 64, 16, "tree"), (3, 43, 9, "tree"), (6, 64, 15, "tree"), (7, 55, 16, "tree"),
+                                        (1, 9, 31, "chain"), (2, 64, 32, "tree"), (2, 3, 33, "tree"), (1, 5, 47, "chain"),
+                                        (2, 64, 48, "tree"), (3, 43, 29, "tree"), (3, 43, 48, "tree"), (2, 3, 49, "tree")])
 def test_round(tw, B, H, N, kind, dtype, state):
     """verify, commit and the fused call (the committed round's draft again) of one case."""
     say("[gpu] small %d x %d units N=%d %s %s tokens %s state" % (B, H, N, kind, dtype, state))
@@ -67,7 +70,8 @@ def test_round(tw, B, H, N, kind, dtype, state):
 
 
 @pytest.mark.parametrize("state", ["f32", "bf16"])
-@pytest.mark.parametrize("units,T", [((1, 1), 1), ((2, 3), 4), ((1, 9), 13), ((2, 64), 16), ((3, 43), 16)])
+@pytest.mark.parametrize("units,T", [((1, 1), 1), ((2, 3), 4), ((1, 9), 13), ((2, 64), 16), ((3, 43), 16), ((1, 5), 17),
+                                     ((2, 3), 31), ((2, 64), 32), ((3, 43), 32)])
 def test_prefill(tw, units, T, state):
     B, H = units
     say("[gpu] small prefill %d x %d units T=%d %s state" % (B, H, T, state))
@@ -108,9 +112,10 @@ def test_commit_path_lengths(tw, L, dtype):
         assert torch.equal(S, d["S0"]) and torch.equal(S_f, d["S0"])
 
 
-def test_malformed(tw):
+@pytest.mark.parametrize("N", [9, 25, 40])
+def test_malformed(tw, N):
     """A bad parent counts as -1, a bad path keeps the state, each with its flag and only for its sequence."""
-    w, case = make(3, 2, 9, "chain", "bf16", 14)
+    w, case = make(3, 2, N, "chain", "bf16", 14)
     par = case.x["parent"].copy()
     par[1, 4], par[1, 7] = 4, -3
     case.x["parent"][1, 4] = case.x["parent"][1, 7] = -1
@@ -123,7 +128,7 @@ def test_malformed(tw):
     o_ref, U_ref, _ = case.oracle()
     assert_close("o", units_of(o, w, case.check), o_ref, TOL["bf16"])
     assert_close("U", units_of(U, w, case.check), U_ref, TOL["bf16"])
-    path = torch.tensor([[0, 1, 2], [0, 2, 1], [0, 1, 9]], dtype=torch.int32, device=DEV)
+    path = torch.tensor([[0, 1, 2], [0, 2, 1], [0, 1, N]], dtype=torch.int32, device=DEV)
     for plen, flags in (([3, 3, 3], [0, 2, 2]), ([3, 2, 2], [0, 0, 0]), ([4, -1, 0], [2, 2, 0])):
         err.zero_()
         S = tw.treewy_commit(d["S0"], U, d["k"], d["alpha"], path, torch.tensor(plen, dtype=torch.int32, device=DEV), err=err)
