@@ -203,7 +203,8 @@ hipError_t launch_commit(const void *S0, const float *U, const void *k, const fl
                          const int32_t *parent, int N, int B, int H, bool f32_k, bool bf16_state,
                          void *S_new, int32_t *err, hipStream_t stream) {
     const int units = B * H;
-    if (small_commit_fits(N, L_max, units)) {
+    // (that kernel reads keys by 16 bytes; the others take any alignment of an element)
+    if (small_commit_fits(N, L_max, units) && (reinterpret_cast<uintptr_t>(k) & 15u) == 0) {
         const CommitArgs cm = {U, k, alpha, path, path_len, parent, S_new, L_max, N, N, N};
         return launch_small_commit(S0, B, H, f32_k, bf16_state, err, cm, stream);
     }

@@ -48,7 +48,10 @@ __global__ __launch_bounds__(THREADS) void snapshot_verify_kernel(
     const float *__restrict__ alpha, const float *__restrict__ beta, const int32_t *__restrict__ parent, int N, int H,
     void *__restrict__ o_, float *snaps, int32_t *__restrict__ err) {
     using In = typename std::conditional<F32IN, float, __bf16>::type;
-    using In4 = typename std::conditional<F32IN, f32x4, bf16x4>::type;
+    // (four entries in one access, of arrays that need no more than an element's alignment)
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef __bf16 bf16x4u __attribute__((ext_vector_type(4), aligned(2)));
+    using In4 = typename std::conditional<F32IN, f32x4u, bf16x4u>::type;
     constexpr int R = ROWS / 2;                          // rows per lane
     const int u = blockIdx.x / PARTS, part = blockIdx.x % PARTS, b = u / H;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;

@@ -137,3 +137,27 @@ def test_malformed(tw, N):
         for b in range(3):
             if flags[b]:
                 assert torch.equal(S[b], d["S0"][b])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_tokens_at_element_alignment(tw, dtype):
+    """Keys (commit) and all tokens (snapshot baseline) that start in the middle of 16 bytes are taken as before."""
+    w, case = make(2, 3, 7, "tree", dtype, 15)
+    d = case.device()
+
+    def shifted(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)
+        buf[1:] = t.flatten()
+        return buf[1:].view(t.shape)
+
+    o, U = tw.treewy_verify(d["S0"], *[d[n] for n in ("q", "k", "v", "alpha", "beta", "parent")])
+    k = shifted(d["k"])
+    assert k.data_ptr() % 16 and k.is_contiguous()
+    S = tw.treewy_commit(d["S0"], U, k, d["alpha"], d["path"], d["path_len"])
+    o_s, states = tw.treewy_snapshot_verify(d["S0"], shifted(d["q"]), k, shifted(d["v"]), d["alpha"], d["beta"], d["parent"],
+                                            o=shifted(o))
+    torch.cuda.synchronize()
+    o_ref, _, st_ref, S_ref = case.oracle(states=True)
+    assert_close("S", units_of(S, w, case.check), S_ref, TOL[dtype])
+    assert_close("o", units_of(o_s, w, case.check), o_ref, TOL[dtype])
+    assert_close("states", units_of(states, w, case.check), st_ref, 1e-5)
