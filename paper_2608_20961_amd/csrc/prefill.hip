@@ -542,10 +542,10 @@ hipError_t launch(const void *S0, const void *q, const void *k, const void *v, c
 // workgroups where that fills at most the GPU (a quarter of the CUs' number
 // of units), to two up to half, and otherwise the resident workgroups walk
 // the units whole.  A chunk step takes 1.3 us with a quarter or half of a
-// unit per workgroup (one 4096-token sequence of 64 heads: 606 -> 180 us,
+// unit per workgroup (one 4096-token sequence of 64 heads: 606 -> 166 us,
 // against verify.hip's kernel, one workgroup of four like waves per unit) and
 // 2.2 to 2.5 us with a whole one (32 sequences of 1000 tokens, 64 heads, bf16
-// state: 812 -> 649 us).
+// state: 807 -> 633 us).
 //   bf16 tokens, one chunk: the kernels of verify.hip and small.hip, whose chunk is bit for bit a verify.
 //   Whole units of few chunks: it too, two of its workgroups per CU hide the
 //     latency of a short unit (512 units of 64 tokens: 25.4 against 26.5 us; of
