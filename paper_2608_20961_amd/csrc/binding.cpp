@@ -106,13 +106,16 @@ PyObject *guarded(PyObject *const *, Py_ssize_t n, Py_ssize_t want, F &&f) {
     }
 }
 
-// The C call itself, without the interpreter lock.
-template <typename F> treewy_status unlocked(F &&f) {
-    treewy_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
-    return st;
+// The C call itself, without the interpreter lock.  Its arguments are values
+// taken before the lock is let go: taking a tensor's pointer can throw (one
+// whose storage gives none out, or a lazy copy that is made there).
+template <typename T> struct Same { using type = T; };
+template <typename... A> treewy_status unlocked(treewy_status (*f)(A...), typename Same<A>::type... a) {
+    struct Unlocked {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Unlocked() { PyEval_RestoreThread(state); }
+    } lock;
+    return f(a...);
 }
 
 constexpr at::ScalarType F32 = at::kFloat, I32 = at::kInt;
@@ -132,11 +135,10 @@ PyObject *verify(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &par = need(a[6], d, I32, {B, N});
         void *err = need_or_null(a[9], d, I32, {B}), *s = stream_of(a[10], d);
         const Tensor o = output(a[7], d, dt, {B, H, N, dv}), U = output(a[8], d, F32, {B, H, N, dv});
-        return result(unlocked([&] {
-            return treewy_verify(ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al), (float *)ptr(be), (int32_t *)ptr(par),
-                                 (int)N, (int)B, (int)H, (int)dk, (int)dv, in, state, ptr(o), (float *)ptr(U),
-                                 (int32_t *)err, s);
-        }), {o, U});
+        const treewy_status st = unlocked(treewy_verify, ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al),
+                                          (float *)ptr(be), (int32_t *)ptr(par), (int)N, (int)B, (int)H, (int)dk,
+                                          (int)dv, in, state, ptr(o), (float *)ptr(U), (int32_t *)err, s);
+        return result(st, {o, U});
     });
 }
 
@@ -156,11 +158,10 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &len = need(a[5], d, I32, {B});
         void *par = need_or_null(a[6], d, I32, {B, N}), *err = need_or_null(a[8], d, I32, {B}), *s = stream_of(a[9], d);
         const Tensor S_new = output(a[7], d, sdt, {B, H, dv, dk});
-        return result(unlocked([&] {
-            return treewy_commit(ptr(S0), (float *)ptr(U), ptr(k), (float *)ptr(al), (int32_t *)ptr(path),
-                                 (int32_t *)ptr(len), (int)L, (int32_t *)par, (int)N, (int)B, (int)H, (int)dk, (int)dv, in,
-                                 state, ptr(S_new), (int32_t *)err, s);
-        }), {S_new});
+        const treewy_status st = unlocked(treewy_commit, ptr(S0), (float *)ptr(U), ptr(k), (float *)ptr(al),
+                                          (int32_t *)ptr(path), (int32_t *)ptr(len), (int)L, (int32_t *)par, (int)N,
+                                          (int)B, (int)H, (int)dk, (int)dv, in, state, ptr(S_new), (int32_t *)err, s);
+        return result(st, {S_new});
     });
 }
 
@@ -189,12 +190,12 @@ PyObject *commit_verify(PyObject *, PyObject *const *a, Py_ssize_t n) {
              *s = stream_of(a[17], d);
         const Tensor S_new = output(a[13], d, sdt, {B, H, dv, dk}), o = output(a[14], d, dt, {B, H, N, dv}),
                      U = output(a[15], d, F32, {B, H, N, dv});
-        return result(unlocked([&] {
-            return treewy_commit_verify(ptr(S), (float *)ptr(Up), ptr(kp), (float *)ptr(alp), (int32_t *)ptr(path),
-                                        (int32_t *)ptr(len), (int)L, (int32_t *)parp, (int)Np, ptr(q), ptr(k), ptr(v),
-                                        (float *)ptr(al), (float *)ptr(be), (int32_t *)ptr(par), (int)N, (int)B, (int)H,
-                                        (int)dk, (int)dv, in, state, ptr(S_new), ptr(o), (float *)ptr(U), (int32_t *)err, s);
-        }), {S_new, o, U});
+        const treewy_status st = unlocked(treewy_commit_verify, ptr(S), (float *)ptr(Up), ptr(kp), (float *)ptr(alp),
+                                          (int32_t *)ptr(path), (int32_t *)ptr(len), (int)L, (int32_t *)parp, (int)Np,
+                                          ptr(q), ptr(k), ptr(v), (float *)ptr(al), (float *)ptr(be),
+                                          (int32_t *)ptr(par), (int)N, (int)B, (int)H, (int)dk, (int)dv, in, state,
+                                          ptr(S_new), ptr(o), (float *)ptr(U), (int32_t *)err, s);
+        return result(st, {S_new, o, U});
     });
 }
 
@@ -212,10 +213,10 @@ PyObject *chain_prefill(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &al = need(a[4], d, F32, {B, H, T}), &be = need(a[5], d, F32, {B, H, T});
         void *err = need_or_null(a[8], d, I32, {B}), *s = stream_of(a[9], d);
         const Tensor S_T = output(a[6], d, sdt, {B, H, dv, dk}), o = output(a[7], d, dt, {B, H, T, dv});
-        return result(unlocked([&] {
-            return treewy_chain_prefill(ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al), (float *)ptr(be), (int)T, (int)B,
-                                        (int)H, (int)dk, (int)dv, in, state, ptr(S_T), ptr(o), (int32_t *)err, s);
-        }), {S_T, o});
+        const treewy_status st = unlocked(treewy_chain_prefill, ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al),
+                                          (float *)ptr(be), (int)T, (int)B, (int)H, (int)dk, (int)dv, in, state,
+                                          ptr(S_T), ptr(o), (int32_t *)err, s);
+        return result(st, {S_T, o});
     });
 }
 
@@ -232,11 +233,11 @@ PyObject *accept_greedy(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &dr = need(a[1], d, I32, {B, N}), &tg = need(a[2], d, I32, {B, N}), &rt = need(a[3], d, I32, {B});
         void *err = need_or_null(a[8], d, I32, {B}), *s = stream_of(a[9], d);
         const Tensor path = output(a[5], d, I32, {B, L}), len = output(a[6], d, I32, {B}), bonus = output(a[7], d, I32, {B});
-        return result(unlocked([&] {
-            return treewy_accept_greedy((int32_t *)ptr(par), (int32_t *)ptr(dr), (int32_t *)ptr(tg), (int32_t *)ptr(rt),
-                                        (int)N, (int)B, (int)L, (int32_t *)ptr(path), (int32_t *)ptr(len),
-                                        (int32_t *)ptr(bonus), (int32_t *)err, s);
-        }), {path, len, bonus});
+        const treewy_status st = unlocked(treewy_accept_greedy, (int32_t *)ptr(par), (int32_t *)ptr(dr),
+                                          (int32_t *)ptr(tg), (int32_t *)ptr(rt), (int)N, (int)B, (int)L,
+                                          (int32_t *)ptr(path), (int32_t *)ptr(len), (int32_t *)ptr(bonus),
+                                          (int32_t *)err, s);
+        return result(st, {path, len, bonus});
     });
 }
 

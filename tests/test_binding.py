@@ -104,3 +104,32 @@ def test_refused_calls_raise_as_the_checks_do(case):
     assert e.value.status == tw.TREEWY_ERR_UNSUPPORTED
     o, _ = bad(q=x["q"].as_subclass(Wrapped))            # taken through Python
     assert torch.equal(o.as_subclass(torch.Tensor), bad()[0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["S0", "q", "k", "v", "alpha", "beta", "parent", "o", "U"])
+def test_a_pointer_that_cannot_be_taken_raises(case, name):
+    """A tensor that is acceptable in every other way but gives out no pointer: the error of the Python checks, from
+    a process that goes on (the native path must hold the interpreter lock where it takes pointers)."""
+    tw, x = case
+    args = {n: x[n].clone() for n in ("S0", "q", "k", "v", "alpha", "beta", "parent")}
+    args.update(o=torch.empty_like(x["v"]), U=torch.empty(x["v"].shape, device="cuda"))
+    torch._C._set_throw_on_mutable_data_ptr(args[name])
+    with pytest.raises(RuntimeError, match="Cannot access data pointer"):
+        tw.treewy_verify(**args)
+    U = torch.zeros(x["v"].shape, device="cuda")
+    path = torch.zeros(x["v"].shape[0], 1, dtype=torch.int32, device="cuda")
+    plen = torch.zeros(x["v"].shape[0], dtype=torch.int32, device="cuda")
+    if name in ("S0", "k", "alpha"):
+        with pytest.raises(RuntimeError, match="Cannot access data pointer"):
+            tw.treewy_commit(args["S0"], U, args["k"], args["alpha"], path, plen)
+    if name not in ("o", "U", "parent"):
+        with pytest.raises(RuntimeError, match="Cannot access data pointer"):
+            tw.treewy_chain_prefill(*[args[n] for n in ("S0", "q", "k", "v", "alpha", "beta")])
+    if name != "parent":
+        with pytest.raises(RuntimeError, match="Cannot access data pointer"):
+            tw.treewy_commit_verify(args["S0"], U, x["k"], x["alpha"], path, plen, *[args[n] for n in
+                                    ("q", "k", "v", "alpha", "beta")], x["parent"], o=args["o"], U=args["U"])
+    o, _ = tw.treewy_verify(*[x[n] for n in ("S0", "q", "k", "v", "alpha", "beta", "parent")])
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(o).all())
