@@ -80,16 +80,35 @@ void *stream_of(PyObject *s, int device) {
     return p;
 }
 
-PyObject *wrap(const Tensor &t) { return THPVariable_Wrap(t); }
-
-PyObject *result(treewy_status st, std::initializer_list<Tensor> out) {
-    if (st != TREEWY_OK) return PyLong_FromLong(st);
-    if (out.size() == 1) return wrap(*out.begin());
-    PyObject *r = PyTuple_New((Py_ssize_t)out.size());
-    Py_ssize_t i = 0;
-    for (const Tensor &t : out) PyTuple_SET_ITEM(r, i++, wrap(t));
-    return r;
-}
+// What the call returns, wrapped before the launch: a failure up to there
+// leaves the call to Python with nothing done, and past it nothing can fail
+// (repeated through Python, a commit in place would be applied twice).
+struct Result {
+    PyObject *r = nullptr;
+    explicit Result(std::initializer_list<Tensor> out) {
+        r = out.size() == 1 ? THPVariable_Wrap(*out.begin()) : PyTuple_New((Py_ssize_t)out.size());
+        if (!r) throw Refused{};
+        if (out.size() == 1) return;
+        Py_ssize_t i = 0;
+        for (const Tensor &t : out) {
+            PyObject *x = THPVariable_Wrap(t);
+            if (!x) {
+                Py_CLEAR(r);
+                throw Refused{};
+            }
+            PyTuple_SET_ITEM(r, i++, x);
+        }
+    }
+    Result(const Result &) = delete;
+    ~Result() { Py_XDECREF(r); }
+    // The result, or the status of a refused call (a small int: always there).
+    PyObject *after(treewy_status st) {
+        if (st != TREEWY_OK) return PyLong_FromLong(st);
+        PyObject *x = r;
+        r = nullptr;
+        return x;
+    }
+};
 
 // Runs f(args, current device); None where it threw.
 template <typename F>
@@ -100,7 +119,7 @@ PyObject *guarded(PyObject *const *, Py_ssize_t n, Py_ssize_t want, F &&f) {
     }
     try {
         return f((int)c10::hip::current_device());
-    } catch (...) {                                      // (also an allocation that failed: Python then says so)
+    } catch (...) {                                      // (nothing is launched yet; an allocation that failed: Python says so)
         PyErr_Clear();
         Py_RETURN_NONE;
     }
@@ -135,10 +154,10 @@ PyObject *verify(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &par = need(a[6], d, I32, {B, N});
         void *err = need_or_null(a[9], d, I32, {B}), *s = stream_of(a[10], d);
         const Tensor o = output(a[7], d, dt, {B, H, N, dv}), U = output(a[8], d, F32, {B, H, N, dv});
-        const treewy_status st = unlocked(treewy_verify, ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al),
-                                          (float *)ptr(be), (int32_t *)ptr(par), (int)N, (int)B, (int)H, (int)dk,
-                                          (int)dv, in, state, ptr(o), (float *)ptr(U), (int32_t *)err, s);
-        return result(st, {o, U});
+        Result result({o, U});
+        return result.after(unlocked(treewy_verify, ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al),
+                                     (float *)ptr(be), (int32_t *)ptr(par), (int)N, (int)B, (int)H, (int)dk,
+                                     (int)dv, in, state, ptr(o), (float *)ptr(U), (int32_t *)err, s));
     });
 }
 
@@ -158,10 +177,10 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &len = need(a[5], d, I32, {B});
         void *par = need_or_null(a[6], d, I32, {B, N}), *err = need_or_null(a[8], d, I32, {B}), *s = stream_of(a[9], d);
         const Tensor S_new = output(a[7], d, sdt, {B, H, dv, dk});
-        const treewy_status st = unlocked(treewy_commit, ptr(S0), (float *)ptr(U), ptr(k), (float *)ptr(al),
-                                          (int32_t *)ptr(path), (int32_t *)ptr(len), (int)L, (int32_t *)par, (int)N,
-                                          (int)B, (int)H, (int)dk, (int)dv, in, state, ptr(S_new), (int32_t *)err, s);
-        return result(st, {S_new});
+        Result result({S_new});
+        return result.after(unlocked(treewy_commit, ptr(S0), (float *)ptr(U), ptr(k), (float *)ptr(al),
+                                     (int32_t *)ptr(path), (int32_t *)ptr(len), (int)L, (int32_t *)par, (int)N,
+                                     (int)B, (int)H, (int)dk, (int)dv, in, state, ptr(S_new), (int32_t *)err, s));
     });
 }
 
@@ -190,12 +209,12 @@ PyObject *commit_verify(PyObject *, PyObject *const *a, Py_ssize_t n) {
              *s = stream_of(a[17], d);
         const Tensor S_new = output(a[13], d, sdt, {B, H, dv, dk}), o = output(a[14], d, dt, {B, H, N, dv}),
                      U = output(a[15], d, F32, {B, H, N, dv});
-        const treewy_status st = unlocked(treewy_commit_verify, ptr(S), (float *)ptr(Up), ptr(kp), (float *)ptr(alp),
-                                          (int32_t *)ptr(path), (int32_t *)ptr(len), (int)L, (int32_t *)parp, (int)Np,
-                                          ptr(q), ptr(k), ptr(v), (float *)ptr(al), (float *)ptr(be),
-                                          (int32_t *)ptr(par), (int)N, (int)B, (int)H, (int)dk, (int)dv, in, state,
-                                          ptr(S_new), ptr(o), (float *)ptr(U), (int32_t *)err, s);
-        return result(st, {S_new, o, U});
+        Result result({S_new, o, U});
+        return result.after(unlocked(treewy_commit_verify, ptr(S), (float *)ptr(Up), ptr(kp), (float *)ptr(alp),
+                                     (int32_t *)ptr(path), (int32_t *)ptr(len), (int)L, (int32_t *)parp, (int)Np,
+                                     ptr(q), ptr(k), ptr(v), (float *)ptr(al), (float *)ptr(be),
+                                     (int32_t *)ptr(par), (int)N, (int)B, (int)H, (int)dk, (int)dv, in, state,
+                                     ptr(S_new), ptr(o), (float *)ptr(U), (int32_t *)err, s));
     });
 }
 
@@ -213,10 +232,10 @@ PyObject *chain_prefill(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &al = need(a[4], d, F32, {B, H, T}), &be = need(a[5], d, F32, {B, H, T});
         void *err = need_or_null(a[8], d, I32, {B}), *s = stream_of(a[9], d);
         const Tensor S_T = output(a[6], d, sdt, {B, H, dv, dk}), o = output(a[7], d, dt, {B, H, T, dv});
-        const treewy_status st = unlocked(treewy_chain_prefill, ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al),
-                                          (float *)ptr(be), (int)T, (int)B, (int)H, (int)dk, (int)dv, in, state,
-                                          ptr(S_T), ptr(o), (int32_t *)err, s);
-        return result(st, {S_T, o});
+        Result result({S_T, o});
+        return result.after(unlocked(treewy_chain_prefill, ptr(S0), ptr(q), ptr(k), ptr(v), (float *)ptr(al),
+                                     (float *)ptr(be), (int)T, (int)B, (int)H, (int)dk, (int)dv, in, state,
+                                     ptr(S_T), ptr(o), (int32_t *)err, s));
     });
 }
 
@@ -233,11 +252,11 @@ PyObject *accept_greedy(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Tensor &dr = need(a[1], d, I32, {B, N}), &tg = need(a[2], d, I32, {B, N}), &rt = need(a[3], d, I32, {B});
         void *err = need_or_null(a[8], d, I32, {B}), *s = stream_of(a[9], d);
         const Tensor path = output(a[5], d, I32, {B, L}), len = output(a[6], d, I32, {B}), bonus = output(a[7], d, I32, {B});
-        const treewy_status st = unlocked(treewy_accept_greedy, (int32_t *)ptr(par), (int32_t *)ptr(dr),
-                                          (int32_t *)ptr(tg), (int32_t *)ptr(rt), (int)N, (int)B, (int)L,
-                                          (int32_t *)ptr(path), (int32_t *)ptr(len), (int32_t *)ptr(bonus),
-                                          (int32_t *)err, s);
-        return result(st, {path, len, bonus});
+        Result result({path, len, bonus});
+        return result.after(unlocked(treewy_accept_greedy, (int32_t *)ptr(par), (int32_t *)ptr(dr),
+                                     (int32_t *)ptr(tg), (int32_t *)ptr(rt), (int)N, (int)B, (int)L,
+                                     (int32_t *)ptr(path), (int32_t *)ptr(len), (int32_t *)ptr(bonus),
+                                     (int32_t *)err, s));
     });
 }
 

@@ -133,3 +133,37 @@ def test_a_pointer_that_cannot_be_taken_raises(case, name):
     o, _ = tw.treewy_verify(*[x[n] for n in ("S0", "q", "k", "v", "alpha", "beta", "parent")])
     torch.cuda.synchronize()
     assert bool(torch.isfinite(o).all())
+
+
+@pytest.mark.gpu
+def test_a_failed_allocation_never_commits_twice(case):
+    """Memory that runs out at any one allocation of an in-place fused call: the state is the old one or the
+    committed one, and the committed one where the call returned (a call repeated after its launch commits twice)."""
+    _testcapi = pytest.importorskip("_testcapi")
+    tw, x = case
+    B, H, N = x["alpha"].shape
+    ver = [x[n] for n in ("q", "k", "v", "alpha", "beta", "parent")]
+    _, U = tw.treewy_verify(x["S0"], *ver)
+    path = torch.zeros(B, 1, dtype=torch.int32, device="cuda")
+    plen = torch.ones(B, dtype=torch.int32, device="cuda")
+    once, _, _ = tw.treewy_commit_verify(x["S0"], U, x["k"], x["alpha"], path, plen, *ver)
+    twice, _, _ = tw.treewy_commit_verify(once, U, x["k"], x["alpha"], path, plen, *ver)
+    torch.cuda.synchronize()
+    assert not torch.equal(once, x["S0"]) and not torch.equal(once, twice)
+    raised = 0
+    for n in range(1, 24):
+        S = x["S0"].clone()
+        kept = [(n, i, n) for i in range(4000)]          # (no tuple of three is left to be used again)
+        _testcapi.set_nomemory(n, n + 1)
+        try:
+            tw.treewy_commit_verify(S, U, x["k"], x["alpha"], path, plen, *ver, S_new=S)
+            done = True
+        except MemoryError:
+            done = False
+        finally:
+            _testcapi.remove_mem_hooks()
+        torch.cuda.synchronize()
+        raised += not done
+        assert torch.equal(S, once) or (not done and torch.equal(S, x["S0"])), (n, done)
+        assert len(kept) == 4000
+    print("raised in %d of 23" % raised, flush=True)
