@@ -44,9 +44,8 @@ inline int compute_units() {
     return cus;
 }
 
-// The kernels of few units (small.hip), and for which sizes they are used.
+// The kernels of few units (small.hip), and for which sizes they are used (verify's rule is the fused call's too).
 bool small_verify_fits(int N, int units, bool f32_in);
-bool small_commit_verify_fits(int N, int units, bool f32_in);
 bool small_prefill_fits(int T, int units, bool f32_in);
 bool small_commit_fits(int N, int L_max, int units);
 hipError_t launch_small_verify(const void *S0, const void *q, const void *k, const void *v, const float *alpha,

@@ -841,7 +841,7 @@ hipError_t dispatch(const void *S0, const void *q, const void *k, const void *v,
     if constexpr (MODE == PREFILL) {
         return bf16_state ? TREEWY_TILES(true, 2) : TREEWY_TILES(false, 2);
     } else {
-        if (N > 16) {                                    // (bf16 tokens: see tiles_fit)
+        if (N > 16) {                                    // (bf16 tokens: see small_verify_fits)
             if (bf16_state) return N <= 32 ? TREEWY_TILES(true, 2) : TREEWY_TILES(true, 3);
             return N <= 32 ? TREEWY_TILES(false, 2) : TREEWY_TILES(false, 3);
         }
@@ -859,8 +859,7 @@ hipError_t dispatch(const void *S0, const void *q, const void *k, const void *v,
 // ones; with many, what every wave repeats (K and Q, the gram, the solve) costs
 // more.  us a call, from a graph, this against the others':
 //   verify, at most 16 nodes: 8-node chains in 32 units 4.5 against 6.6, 128 units
-//     5.0 against 7.5, 384 units 8.5 against 11.0; 16-node trees in 384 units 10.0
-//     against 11.3, 512 units 12.0 both, 1024 units 22.0 against 20.2;
+//     5.0 against 7.5;
 //   verify, more nodes, bf16 tokens: 32 nodes in 64 units 6.6 against 7.2, 128 units
 //     7.0 against 7.8, 192 units 10.7 against 8.1; 39 and 48 nodes in 128 units 8.1
 //     and 9.0 against 9.9 and 11.1, 192 units 11.6 and 13.9 against 10.3 and 11.7; 64
@@ -873,14 +872,14 @@ hipError_t dispatch(const void *S0, const void *q, const void *k, const void *v,
 //     units 11.7 against 11.3;
 //   commit: 32 units 4.9 against 5.3, 128 units 6.4 to 6.7 against 6.7, 256 units
 //     10.4 against 8.1 (the state's rows pass in 64-byte pieces).
+// One limit for verify, the fused call and a one-chunk prompt: their kernels of
+// one family do the same arithmetic, so a fused call that commits nothing, and
+// a prompt of one chunk, give verify's outputs bit for bit at every number of
+// units.  It costs verify of at most 16 nodes up to 384 units (8-node chains
+// in 256 units 6.1 against 7.3, in 384 units 8.5 against 11.0; with fp32 tokens
+// 16-node trees in 192 units 9.2 against 8.2).
 static bool few_units(int units) { return 2 * (int64_t)units <= compute_units(); }
-static bool tiles_fit(int N, int units, bool f32_in) { return N > 16 && N <= 48 && !f32_in && few_units(units); }
-bool small_verify_fits(int N, int units, bool f32_in) {
-    return (N <= 16 && 2 * (int64_t)units <= 3 * (int64_t)compute_units()) || tiles_fit(N, units, f32_in);
-}
-bool small_commit_verify_fits(int N, int units, bool f32_in) {
-    return (N <= 16 && few_units(units)) || tiles_fit(N, units, f32_in);
-}
+bool small_verify_fits(int N, int units, bool f32_in) { return N <= (f32_in ? 16 : 48) && few_units(units); }
 bool small_prefill_fits(int T, int units, bool f32_in) { return T <= 32 && !f32_in && few_units(units); }
 bool small_commit_fits(int N, int L_max, int units) { return N <= 64 && L_max <= 64 && few_units(units); }
 

@@ -1592,7 +1592,7 @@ hipError_t launch_commit_verify(const void *S_old, const float *U_prev, const vo
                                 void *S_new, void *o, float *U, int32_t *err, hipStream_t stream) {
     const CommitArgs cm = {U_prev, k_prev, alpha_prev, path, path_len, parent_prev, S_new, L_max, N_prev,
                            N_prev, N_prev};
-    if (small_commit_verify_fits(N, B * H, f32_in))
+    if (small_verify_fits(N, B * H, f32_in))
         return launch_small_commit_verify(S_old, q, k, v, alpha, beta, parent, N, B, H, f32_in, bf16_state, o, U, err, cm,
                                           stream);
     return dispatch<true>(S_old, q, k, v, alpha, beta, parent, N, N, N, B, H, f32_in, bf16_state, o, U, err, cm,

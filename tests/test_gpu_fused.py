@@ -212,6 +212,35 @@ def test_fused_empty_path_is_plain_verify(tw):
     assert torch.equal(o, o_v) and torch.equal(U, U_v)
 
 
+@pytest.mark.parametrize("dtype,state", [("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32")])
+@pytest.mark.parametrize("B,H", [(2, 3), (2, 64), (3, 43), (4, 64), (6, 64), (5, 77)])
+def test_empty_path_and_one_chunk_are_verify_at_every_size(tw, B, H, dtype, state):
+    """Nothing accepted, and a prompt of one chunk of bf16 tokens: verify's outputs bit for bit, whichever kernels
+    the node and unit counts choose (6, 128, 129, 256, 384 and 385 units of 256 CUs)."""
+    say("[gpu] %d units, %s tokens, %s state: the fused call with an empty path and prefill against verify" % (B * H, dtype, state))
+    g = torch.Generator(device=DEV).manual_seed(B * H)
+    dt, sdt = (torch.bfloat16 if t == "bf16" else torch.float32 for t in (dtype, state))
+    unit = lambda x: x / x.norm(dim=-1, keepdim=True)
+    r = lambda *s: torch.randn(*s, generator=g, device=DEV)
+    S0 = (0.2 * r(B, H, 128, 128)).to(sdt)
+    for N in (1, 8, 16, 17, 32, 33, 48, 49, 64):
+        q, k, v = unit(r(B, H, N, 128)).to(dt), unit(r(B, H, N, 128)).to(dt), r(B, H, N, 128).to(dt)
+        alpha, beta = (lo + w * torch.rand(B, H, N, generator=g, device=DEV) for lo, w in ((0.85, 0.149), (0.05, 0.9)))
+        for parent in (np.arange(-1, N - 1), (np.arange(N) - 1) // 2):
+            par = torch.from_numpy(np.tile(np.maximum(parent, -1).astype(np.int32), (B, 1))).to(DEV)
+            par[:, 0] = -1
+            o, U = tw.treewy_verify(S0, q, k, v, alpha, beta, par)
+            none = torch.zeros(B, dtype=torch.int32, device=DEV)
+            S_new, o_f, U_f = tw.treewy_commit_verify(S0, U, k, alpha, par[:, :1].contiguous(), none, q, k, v, alpha, beta, par)
+            torch.cuda.synchronize()
+            assert torch.equal(S_new, S0), N
+            assert torch.equal(o, o_f) and torch.equal(U, U_f), N
+            if dtype == "bf16" and N <= 32 and int(par[0, -1]) == N - 2:
+                _, o_p = tw.treewy_chain_prefill(S0, q, k, v, alpha, beta)
+                torch.cuda.synchronize()
+                assert torch.equal(o, o_p), N
+
+
 def test_fused_bad_path_keeps_state(tw):
     w = wl.scaled(wl.WORKLOADS[2], B=4, H=2)
     xp = wl.make_inputs(w, seed=61, cfg_key=361)
