@@ -126,36 +126,46 @@ struct State {
     }
 };
 
-// Key rows, NK at a time so that one latency covers them, each with a factor of this lane's column.
+// x[i] += u k[i], i = 0 .. 15, where k[2 j], k[2 j + 1] are the values k0, k1 of lane L + j of each row of 16 lanes (see fmac_bcast).
+template <int L> __device__ __forceinline__ void rank1_half(float (&x0)[8], float (&x1)[8], float k0, float k1, float u) {
+#define TW_F(n, m, j) "v_fmac_f32_dpp %" #n ", %" #m ", %[u] row_newbcast:%[i" #j "] row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t" TW_F(0, 16, 0) TW_F(1, 17, 0) TW_F(2, 16, 1) TW_F(3, 17, 1) TW_F(4, 16, 2) TW_F(5, 17, 2)
+        TW_F(6, 16, 3) TW_F(7, 17, 3) TW_F(8, 16, 4) TW_F(9, 17, 4) TW_F(10, 16, 5) TW_F(11, 17, 5) TW_F(12, 16, 6)
+        TW_F(13, 17, 6) TW_F(14, 16, 7) TW_F(15, 17, 7)
+        : "+&v"(x0[0]), "+&v"(x0[1]), "+&v"(x0[2]), "+&v"(x0[3]), "+&v"(x0[4]), "+&v"(x0[5]), "+&v"(x0[6]), "+&v"(x0[7]),
+          "+&v"(x1[0]), "+&v"(x1[1]), "+&v"(x1[2]), "+&v"(x1[3]), "+&v"(x1[4]), "+&v"(x1[5]), "+&v"(x1[6]), "+&v"(x1[7])
+        : "v"(k0), "v"(k1), [u] "v"(u), [i0] "n"(L), [i1] "n"(L + 1), [i2] "n"(L + 2), [i3] "n"(L + 3), [i4] "n"(L + 4),
+          [i5] "n"(L + 5), [i6] "n"(L + 6), [i7] "n"(L + 7));
+#undef TW_F
+}
+
+// NK entries of a path, read together so that one latency covers them: the key
+// row, two values a lane, and the pseudo-value of this lane's column.  Lane
+// (l16, g) holds d_k 32 (l16 / 4) + 8 g + 2 (l16 % 4) + [0, 2), so the 32 values
+// that lane group g needs (those of its state entries) are in its own 16 lanes, and the
+// multiply-adds take them by a row broadcast.  (With each lane holding all
+// of its 32 values, a key row was four or eight reads and as many registers,
+// and a path of 64 entries a chain of 16 or 32 latencies: the fused call of 128
+// units of 8 nodes took 21.8 us with bf16 and 30.5 us with fp32 tokens.)
 template <bool F32IN, int NK>
 struct Keys {
-    static constexpr int XN = F32IN ? 2 : 1, SZ = F32IN ? 4 : 2;
-    uint4 k[NK][4][XN];
+    static constexpr int SZ = F32IN ? 4 : 2;
+    using KT = typename std::conditional<F32IN, uint2, uint32_t>::type;
+    KT k[NK];
     float u[NK];
-    __device__ __forceinline__ void load(int e, rsrc_t r, int row, int g) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int p = 0; p < XN; ++p) k[e][s][p] = ld_u32x4<CACHED>(r, row + (32 * s + 8 * g) * SZ + 16 * p);
-    }
-    // x[s][i] += wu k[32 s + 8 g + i]
+    // x += wu k^T
     __device__ __forceinline__ void rank1(float (&x)[4][8], float wu, int e) const {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            float k8[8];
-            if constexpr (F32IN) {
-                floats8(k[e][s][0], k[e][s][XN - 1], k8);
-            } else {
-                const uint32_t w[4] = {k[e][s][0].x, k[e][s][0].y, k[e][s][0].z, k[e][s][0].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    k8[2 * i] = __builtin_bit_cast(float, w[i] << 16);
-                    k8[2 * i + 1] = __builtin_bit_cast(float, w[i] & 0xffff0000u);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[s][i] = fmaf(wu, k8[i], x[s][i]);
+        float k0, k1;
+        if constexpr (F32IN) {
+            const uint32_t a = k[e].x, b = k[e].y;
+            k0 = __builtin_bit_cast(float, a);
+            k1 = __builtin_bit_cast(float, b);
+        } else {
+            k0 = __builtin_bit_cast(float, k[e] << 16);
+            k1 = __builtin_bit_cast(float, k[e] & 0xffff0000u);
         }
+        rank1_half<0>(x[0], x[1], k0, k1, wu);
+        rank1_half<8>(x[2], x[3], k0, k1, wu);
     }
 };
 
@@ -210,29 +220,40 @@ struct Path {
     template <bool F32IN, int NK>
     __device__ __forceinline__ void load(Keys<F32IN, NK> &x, int l0, int g, int col) const {
         constexpr int OOB = 1 << 30;
+        const int l16 = threadIdx.x & 15, off = (32 * (l16 >> 2) + 8 * g + 2 * (l16 & 3)) * x.SZ;
 #pragma unroll
         for (int e = 0; e < NK; ++e) {
             const bool live = l0 + e < len;              // (uniform)
             const int a = __builtin_amdgcn_readlane(node, (l0 + e) & 63);
-            x.load(e, rk, live ? a * row : OOB, g);
+            if constexpr (F32IN) x.k[e] = ld_u32x2<CACHED>(rk, (live ? a * row : OOB) + off);
+            else x.k[e] = (uint32_t)ld_i32(rk, (live ? a * row : OOB) + off);
             x.u[e] = ld_f32(ru, live ? (a * D + col) * 4 : OOB);
         }
     }
     __device__ __forceinline__ float weight(int l) const {
-        return l < len ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), l & 63)) : 0.f;
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), l & 63));
     }
 };
 
-// S <- g_a S + sum_l w_l U_l k_l^T over the path, whose first entries are in `keys`.
-template <bool F32IN, bool SBF, int NK>
-__device__ __forceinline__ void commit_path(State<SBF> &st, const Path &path, Keys<F32IN, NK> &keys) {
+// S <- g_a S + sum_l w_l U_l k_l^T over the path, entry after entry; the first are in `keys`, the others come
+// MORE at a time while those before them are added.
+constexpr int FIRST = 8, MORE = 16;
+template <bool F32IN, bool SBF>
+__device__ __forceinline__ void commit_path(State<SBF> &st, const Path &path, const Keys<F32IN, FIRST> &keys) {
     if (path.len == 0) return;                           // (uniform; the state stays as it is, bit for bit)
+    Keys<F32IN, MORE> now, next;
+    if (path.len > FIRST) path.load(now, FIRST, st.g, st.col);
     float x[4][8];
     st.get(x, path.ga);
-    for (int l0 = 0; l0 < path.len; l0 += NK) {
-        if (l0 > 0) path.template load<F32IN>(keys, l0, st.g, st.col);
 #pragma unroll
-        for (int e = 0; e < NK; ++e) keys.rank1(x, path.weight(l0 + e) * keys.u[e], e);
+    for (int e = 0; e < FIRST; ++e)
+        if (e < path.len) keys.rank1(x, path.weight(e) * keys.u[e], e);
+    for (int l0 = FIRST; l0 < path.len; l0 += MORE) {
+        if (l0 + MORE < path.len) path.load(next, l0 + MORE, st.g, st.col);
+#pragma unroll
+        for (int e = 0; e < MORE; ++e)
+            if (l0 + e < path.len) now.rank1(x, path.weight(l0 + e) * now.u[e], e);
+        now = next;
     }
     st.put(x);
 }
@@ -321,10 +342,10 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
         b4[r] = __shfl(bt, src);
     }
 
-    Keys<F32IN, F32IN ? 2 : 4> keys;
+    Keys<F32IN, FIRST> keys;
     if constexpr (MODE == FUSED) {
         path.check(cm, b, first, err);
-        path.template load<F32IN>(keys, 0, g, col);
+        path.load(keys, 0, g, col);
     }
 
     // ---- gram tiles: lane t = l16, rows i = 4 g + r -------------------------------
@@ -585,10 +606,10 @@ __global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void til
     lds_order();
     auto field1 = [&](int f, int a) { return node_s[wave][f][16 * a + l16]; };
     auto field4 = [&](int f, int a) { return *reinterpret_cast<const int4 *>(&node_s[wave][f][16 * a + 4 * g]); };
-    Keys<false, 4> keys;
+    Keys<false, FIRST> keys;
     if constexpr (MODE == FUSED) {
         path.check(cm, b, first, err);
-        path.template load<false>(keys, 0, g, col);
+        path.load(keys, 0, g, col);
     }
 
     // ---- gram tiles: lane t = 16 a + l16, rows i = 16 bb + 4 g + r, bb <= a --------
@@ -805,8 +826,8 @@ __global__ __launch_bounds__(64 * NW) void small_commit_kernel(const void *S0, i
     st.load(S0, u);
     __builtin_amdgcn_sched_barrier(0);
     path.check(cm, b, part == 0 && wave == 0, err);
-    Keys<F32IN, F32IN ? 2 : 4> keys;
-    path.template load<F32IN>(keys, 0, g, col);
+    Keys<F32IN, FIRST> keys;
+    path.load(keys, 0, g, col);
     commit_path(st, path, keys);
     st.store(cm.S_new, u);
 }
@@ -857,27 +878,28 @@ hipError_t dispatch(const void *S0, const void *q, const void *k, const void *v,
 // Where these kernels are used: with few units a call is one wave's chain of
 // dependent steps and a launch, and eight short waves per unit beat four long
 // ones; with many, what every wave repeats (K and Q, the gram, the solve) costs
-// more.  us a call, from a graph, this against the others':
-//   verify, at most 16 nodes: 8-node chains in 32 units 4.5 against 6.6, 128 units
-//     5.0 against 7.5;
-//   verify, more nodes, bf16 tokens: 32 nodes in 64 units 6.6 against 7.2, 128 units
-//     7.0 against 7.8, 192 units 10.7 against 8.1; 39 and 48 nodes in 128 units 8.1
-//     and 9.0 against 9.9 and 11.1, 192 units 11.6 and 13.9 against 10.3 and 11.7; 64
-//     nodes in four tiles 11.2 against 10.6 already at 64 units, 24 nodes with fp32
-//     tokens 8.7 against 8.5;
-//   the fused call: 8-node chains in 32 units 6.6 against 10.0, 128 units 8.8 against
-//     11.1, 256 units 12.0 both; 32 nodes in 128 units 10.7 against 11.2, 192 units
-//     15.7 against 12.0;
-//   prefill of 20 tokens: 64 units 8.2 against 10.3, 128 units 9.2 against 10.9, 192
-//     units 11.7 against 11.3;
-//   commit: 32 units 4.9 against 5.3, 128 units 6.4 to 6.7 against 6.7, 256 units
-//     10.4 against 8.1 (the state's rows pass in 64-byte pieces).
+// more.  us a call, from a graph, this against the others' (fp32 state):
+//   verify: 8-node chains in 32 units 4.1 against 6.2, 128 units 4.2 against 6.4;
+//     32 nodes, bf16 tokens, in 128 units 6.5 against 8.0, 192 units 10.0 against
+//     7.9; 39 and 48 nodes in 128 units 8.0 and 8.5 against 11.1 and 11.2, 192
+//     units 12.3 and 13.2 against 11.4 and 11.7; 64 nodes in four tiles 11.2
+//     against 10.6 already at 64 units, 24 nodes with fp32 tokens 8.7 against 8.5;
+//   the fused call, paths of 4 entries: 8-node chains in 32 units 5.9 against 9.8, 128
+//     units 7.1 against 10.2; 32 nodes in 128 units 9.3 against 11.7, 192 units 13.9
+//     against 12.0; paths of 64 entries, 8 nodes in 128 units: 15.0 against 16.9 with
+//     bf16 and 15.8 against 19.2 with fp32 tokens;
+//   prefill of 20 tokens: 64 units 7.7 against 9.8, 128 units 9.0 against 10.3, 192
+//     units 12.0 against 10.7;
+//   commit, paths of 0, 1 and 4 entries: 32 units 3.7, 4.1 and 4.4 against 3.7, 4.5
+//     and 5.3, 128 units 4.6, 5.3 and 5.6 against 4.5, 5.4 and 6.2, 192 units 6.9, 7.5
+//     and 7.7 against 4.8, 5.6 and 6.6 (the state's rows pass in 64-byte pieces).
 // One limit for verify, the fused call and a one-chunk prompt: their kernels of
 // one family do the same arithmetic, so a fused call that commits nothing, and
 // a prompt of one chunk, give verify's outputs bit for bit at every number of
-// units.  It costs verify of at most 16 nodes up to 384 units (8-node chains
-// in 256 units 6.1 against 7.3, in 384 units 8.5 against 11.0; with fp32 tokens
-// 16-node trees in 192 units 9.2 against 8.2).
+// units.  Past it a draft of at most 16 nodes could gain still (8-node chains in
+// 256 units: verify 5.9 against 7.1, fused 9.7 against 11.8) where a prompt of 16
+// tokens loses (192 units 11.8 against 11.0), and with fp32 tokens 16-node trees in
+// 192 units lose too (9.2 against 8.2).
 static bool few_units(int units) { return 2 * (int64_t)units <= compute_units(); }
 bool small_verify_fits(int N, int units, bool f32_in) { return N <= (f32_in ? 16 : 48) && few_units(units); }
 bool small_prefill_fits(int T, int units, bool f32_in) { return T <= 32 && !f32_in && few_units(units); }
