@@ -6,8 +6,10 @@ code only) against the installed torch (both in-tree).
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+from typing import Optional
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -25,16 +27,20 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-I", INCLUDE, "-I", CSRC]
 
 
-def binding_command(obj: str) -> list:
-    """g++ over binding.cpp (no device code) with torch's and HIP's headers."""
+def binding_command(obj: str) -> Optional[list]:
+    """g++ over binding.cpp (no device code) with torch's and HIP's headers; None where torch is not installed."""
     import sysconfig
 
-    import torch
-    from torch.utils import cpp_extension
-    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include", INCLUDE]
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-w", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+    try:
+        import torch
+        from torch.utils import cpp_extension
+    except ImportError:
+        return None
+    rocm = os.path.dirname(os.path.dirname(shutil.which(HIPCC) or "/opt/rocm/bin/hipcc"))
+    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(rocm, "include")]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *[x for i in inc for x in ("-isystem", i)],
-            "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj]
+            "-I", INCLUDE, "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj]
 
 
 def link_binding(obj: str) -> None:
@@ -48,33 +54,37 @@ def link_binding(obj: str) -> None:
 
 
 def build(verbose: bool = False) -> str:
+    """Both libraries; where torch is not installed the C-ABI library alone."""
     os.makedirs(OBJDIR, exist_ok=True)
-    procs = []
+    objs = [os.path.join(OBJDIR, src.replace(".hip", ".o")) for src in SOURCES]
+    commands = {src: [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj] for src, obj in zip(SOURCES, objs)}
     binding_obj = os.path.join(OBJDIR, "binding.o")
-    procs.append(("binding.cpp", subprocess.Popen(binding_command(binding_obj), stdout=subprocess.PIPE,
-                                                  stderr=subprocess.STDOUT, text=True)))
-    objs = []
-    for src in SOURCES:
-        obj = os.path.join(OBJDIR, src.replace(".hip", ".o"))
-        objs.append(obj)
-        cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    binding = binding_command(binding_obj)
+    if binding:
+        commands["binding.cpp"] = binding
+    procs = {}
+    for src, cmd in commands.items():
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+        procs[src] = subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     failed = []
-    for src, p in procs:
+    for src, p in procs.items():
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if out.strip() and (verbose or p.returncode):
             print(out, file=sys.stderr)
         if p.returncode:
             failed.append(src)
+    if set(failed) <= {"binding.cpp"}:                   # (the library does not depend on the binding)
+        tmp = LIB + ".tmp%d" % os.getpid()
+        subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
+        os.replace(tmp, LIB)
     if failed:
-        raise RuntimeError("hipcc failed on " + ", ".join(failed))
-    tmp = LIB + ".tmp%d" % os.getpid()
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
-    os.replace(tmp, LIB)
-    link_binding(binding_obj)
+        raise RuntimeError("the compiler failed on " + ", ".join(failed))
+    if binding:
+        link_binding(binding_obj)
+    else:
+        print("torch is not installed: built %s without the Python binding's native call path" % LIB, file=sys.stderr)
     return LIB
 
 

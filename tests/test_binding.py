@@ -1,9 +1,55 @@
 """The native call path (csrc/binding.cpp) takes exactly the calls that the
 Python checks accept: what it does not take runs through them and raises what
 they raise, and what both can run gives the same outputs."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.parametrize("binding", ["missing", "broken"])
+def test_the_library_alone_imports(tmp_path, binding):
+    """libtreewy.so without a native call path that loads: a warning with the build command, and the Python checks."""
+    from paper_2608_20961_amd import treewy as tw
+    pkg = tmp_path / "paper_2608_20961_amd"
+    pkg.mkdir()
+    for n in ("__init__.py", "treewy.py", "libtreewy.so"):
+        shutil.copy(os.path.join(os.path.dirname(tw.__file__), n), pkg / n)
+    if binding == "broken":
+        (pkg / "_binding.so").write_bytes(b"not a library")
+    code = ("import warnings, torch\n"
+            "with warnings.catch_warnings(record=True) as said:\n"
+            "    warnings.simplefilter('always')\n"
+            "    from paper_2608_20961_amd import treewy as tw\n"
+            "assert any('python -m paper_2608_20961_amd.build' in str(w.message) for w in said), said\n"
+            "x, g = torch.zeros(1, 1, 2, 128), torch.zeros(1, 1, 2)\n"
+            "try:\n"
+            "    tw.treewy_verify(torch.zeros(1, 1, 128, 128), x, x, x, g, g, torch.zeros(1, 2, dtype=torch.int32))\n"
+            "except ValueError as e:\n"
+            "    assert 'must be on a GPU' in str(e)\n"
+            "    print('imported')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=240)
+    assert r.stdout.strip() == "imported", r.stderr[-2000:]
+
+
+def test_the_library_builds_without_torch():
+    """binding_command says so where torch is not there, in place of an ImportError before anything is compiled."""
+    code = ("import sys\nsys.modules['torch'] = None\n"
+            "from paper_2608_20961_amd import build\nassert build.binding_command('x.o') is None\nprint('fine')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=60)
+    assert r.stdout.strip() == "fine", r.stderr[-2000:]
+
+
+@pytest.mark.gpu
+def test_the_native_path_is_loaded():
+    from paper_2608_20961_amd import treewy as tw
+    assert os.path.basename(tw._binding.__file__) == "_binding.so"
 
 
 def test_cpu_tensors_are_left_to_the_checks():
