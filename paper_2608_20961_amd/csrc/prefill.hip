@@ -541,12 +541,16 @@ hipError_t launch(const void *S0, const void *q, const void *k, const void *v, c
 // One workgroup of this kernel runs on a CU, so a unit goes to four
 // workgroups where that fills at most the GPU (a quarter of the CUs' number
 // of units), to two up to half, and otherwise the resident workgroups walk
-// the units whole.  A chunk step takes 1.3 us with a quarter or half of a
-// unit per workgroup (one 4096-token sequence of 64 heads: 606 -> 166 us,
-// against verify.hip's kernel, one workgroup of four like waves per unit) and
-// 2.2 to 2.5 us with a whole one (32 sequences of 1000 tokens, 64 heads, bf16
-// state: 807 -> 633 us).
-//   bf16 tokens, one chunk: the kernels of verify.hip and small.hip, whose chunk is bit for bit a verify.
+// the units whole.  With bf16 tokens a chunk step takes 1.3 us with a quarter or
+// half of a unit per workgroup (one 4096-token sequence of 64 heads: 606 -> 166
+// us, against verify.hip's kernel, one workgroup of four like waves per unit;
+// bound by the state waves' serial chain) and 2.2 to 2.5 us with a whole one (32
+// sequences of 1000 tokens, 64 heads, bf16 state: 807 -> 633 us).  With fp32 tokens
+// a step takes 2.9 us (64 units of 777 tokens: 185 -> 78.6 us): there the chunk
+// waves set the pace, each loading, splitting and staging 32 KB of K and Q and
+// making three products for one, with three slots in LDS instead of four.
+//   bf16 tokens, one chunk: the kernels of verify.hip and small.hip, whose chunk is bit for bit a verify
+//     (small.hip's limit is one for both calls).
 //   Whole units of few chunks: it too, two of its workgroups per CU hide the
 //     latency of a short unit (512 units of 64 tokens: 25.4 against 26.5 us; of
 //     512 tokens: 124 against 105 us; in one round of at most as many units as

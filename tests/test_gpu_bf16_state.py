@@ -70,14 +70,17 @@ def test_ragged(tw, N):
     run_case(tw, bf16_case(w, N, 600 + N), "ragged N=%d" % N)
 
 
-@pytest.mark.parametrize("kind,N,depth", [("chain", 12, 12), ("chain", 33, 33), ("chain", 64, 64), ("tree", 64, 14)])
-def test_solves(tw, kind, N, depth):
+@pytest.mark.parametrize("B,H", [(2, 3), (3, 43)])
+@pytest.mark.parametrize("kind,N,depth", [("chain", 12, 12), ("chain", 32, 32), ("chain", 33, 33), ("chain", 64, 64),
+                                          ("tree", 64, 14)])
+def test_solves(tw, kind, N, depth, B, H):
     """Trees taking the medium solve (chain of 12, 64-node tree of depth 14)
-    and the dense sweep (chains of 33 and 64) with a bf16 state."""
+    and the dense sweep (chains of 32, 33 and 64) with a bf16 state, in 129 units.
+    In 6 units drafts of at most 48 nodes run the kernels of few units."""
     order = "chain_depth_0_to_N" if kind == "chain" else "uniform_node"
-    w = wl.Workload(kind, 2, 3, N, 128, 128, "bf16", kind, depth, (1,) if kind == "chain" else (3,), (0.85, 0.999),
+    w = wl.Workload(kind, B, H, N, 128, 128, "bf16", kind, depth, (1,) if kind == "chain" else (3,), (0.85, 0.999),
                     (0.05, 0.95), 16, order)
-    run_case(tw, bf16_case(w, N, 650 + N), "%s N=%d depth %d" % (kind, N, depth))
+    run_case(tw, bf16_case(w, N, 650 + N, wl.sample_units(w, 6)), "%s N=%d depth %d, %d units" % (kind, N, depth, w.units))
 
 
 def test_bit_identical_to_fp32_state_with_bf16_values(tw):

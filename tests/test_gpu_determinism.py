@@ -64,12 +64,17 @@ def _same(label, runs):
             assert torch.equal(a, b), "%s: output %d of run %d differs from run 0" % (label, j, i)
 
 
-@pytest.mark.parametrize("state", ["f32", "bf16"])
-def test_chain_prefill_deterministic(tw, state):
-    S0, q, k, v, alpha, beta = _inputs(32, 16, 200, seed=1)
+@pytest.mark.parametrize("tokens,state,B,H,T", [
+    ("bf16", "f32", 32, 16, 200), ("bf16", "bf16", 32, 16, 200),                                   # whole units
+    ("bf16", "f32", 4, 16, 200), ("bf16", "bf16", 4, 16, 200), ("f32", "f32", 4, 16, 200),         # quarters of a unit
+    ("bf16", "f32", 8, 16, 200), ("bf16", "bf16", 8, 16, 200), ("f32", "f32", 8, 16, 200),         # halves
+    ("bf16", "f32", 32, 16, 128), ("bf16", "bf16", 32, 16, 128), ("f32", "f32", 32, 16, 200),      # one workgroup per unit
+    ("bf16", "f32", 8, 16, 32), ("bf16", "bf16", 8, 16, 32)])                                      # few units
+def test_chain_prefill_deterministic(tw, tokens, state, B, H, T):
+    S0, q, k, v, alpha, beta = _inputs(B, H, T, seed=1, dt=torch.bfloat16 if tokens == "bf16" else torch.float32)
     if state == "bf16":
         S0 = S0.to(torch.bfloat16)
-    say("[gpu] determinism: chain prefill, 512 units x 200 tokens, %s state" % state)
+    say("[gpu] determinism: chain prefill, %d units x %d %s tokens, %s state" % (B * H, T, tokens, state))
     runs = []
     for _ in range(RUNS):
         S_T, o = tw.treewy_chain_prefill(S0, q, k, v, alpha, beta)
@@ -79,14 +84,14 @@ def test_chain_prefill_deterministic(tw, state):
 
 
 @pytest.mark.parametrize("state", ["f32", "bf16"])
-def test_fused_deterministic(tw, state):
-    B, H, N = 32, 32, 64
+@pytest.mark.parametrize("B,H,N", [(32, 32, 64), (8, 16, 48), (8, 16, 32), (8, 16, 16)])
+def test_fused_deterministic(tw, state, B, H, N):
     S0, q, k, v, alpha, beta = _inputs(B, H, N, seed=2)
     if state == "bf16":
         S0 = S0.to(torch.bfloat16)
     parent, path, plen = _tree(B, N, seed=2)
     _, U_prev = tw.treewy_verify(S0, q, k, v, alpha, beta, parent)
-    say("[gpu] determinism: fused commit -> verify, 1024 units x 64 nodes, %s state" % state)
+    say("[gpu] determinism: fused commit -> verify, %d units x %d nodes, %s state" % (B * H, N, state))
     runs = []
     for _ in range(RUNS):
         S_new, o, U = tw.treewy_commit_verify(S0, U_prev, k, alpha, path, plen, q, k, v, alpha, beta, parent,

@@ -62,6 +62,14 @@ def test_chain64(tw, state):
     check(tw, Case(w, seed=1, cfg_key=2100), "fast-decay chain of 64", state)
 
 
+@pytest.mark.parametrize("B,H", [(2, 3), (3, 43)])
+@pytest.mark.parametrize("N,dtype,state", [(16, "bf16", "f32"), (16, "f32", "f32"), (32, "bf16", "bf16"), (48, "bf16", "f32")])
+def test_shorter_chains(tw, N, dtype, state, B, H):
+    """The kernels of few units (6 units) and, of the same drafts, the others (129)."""
+    w = fast_workload(N, N, dtype, B, H, caps=(1,), accept="chain_depth_0_to_N")
+    check(tw, Case(w, seed=9, cfg_key=2109, check_units=wl.sample_units(w, 6)), "fast-decay chain of %d, %d units" % (N, w.units), state)
+
+
 def test_chain64_f32_inputs(tw):
     w = fast_workload(64, 64, "f32", caps=(1,), accept="chain_depth_0_to_N")
     check(tw, Case(w, seed=2, cfg_key=2101), "fast-decay f32 chain of 64")
@@ -85,16 +93,21 @@ def test_shallow_tree64(tw):
     check(tw, Case(w, seed=5, cfg_key=2104), "fast-decay tree of 64, depth 8")
 
 
-@pytest.mark.parametrize("dtype,state", [("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32")])
-def test_prefill130(tw, dtype, state):
-    T = 130
-    w = fast_workload(T, T, dtype, caps=(1,), accept="chain_depth_0_to_N")
+@pytest.mark.parametrize("dtype,state,B,H,T", [("bf16", "f32", 2, 3, 130), ("bf16", "bf16", 2, 3, 130), ("f32", "f32", 2, 3, 130),
+                                               ("f32", "f32", 3, 43, 200), ("bf16", "bf16", 1, 257, 97), ("bf16", "f32", 3, 43, 130),
+                                               ("bf16", "f32", 1, 5, 32)])
+def test_prefill130(tw, dtype, state, B, H, T):
+    """By columns (6 units), whole units (129, bf16), one workgroup per unit (129 of fp32 tokens, 257), few units (32 tokens)."""
+    w = fast_workload(T, T, dtype, B, H, caps=(1,), accept="chain_depth_0_to_N")
     x = wl.make_inputs(w, seed=6, cfg_key=2105)
     n = w.units
-    S0 = warm_state(w, np.arange(n), 6, 2106)
+    units = wl.sample_units(w, 6)
+    S_chk = warm_state(w, units, 6, 2106)
     if state == "bf16":
-        S0 = wl.round_to_bf16(S0)
-    say("[gpu] fast-decay prefill T=%d %s inputs, %s state" % (T, dtype, state))
+        S_chk = wl.round_to_bf16(S_chk)
+    S0 = S_chk[np.searchsorted(units, np.arange(n)) % len(units)]
+    S0[units] = S_chk
+    say("[gpu] fast-decay prefill T=%d %s inputs, %s state, %d units" % (T, dtype, state, n))
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     sdt = torch.bfloat16 if state == "bf16" else torch.float32
     dev = lambda a, d=torch.float32: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(DEV).to(d)
@@ -104,13 +117,14 @@ def test_prefill130(tw, dtype, state):
                                      dev(x["beta"]), err=err)
     torch.cuda.synchronize()
     assert int(err.abs().sum()) == 0
-    uv = lambda a: a.reshape(n, *a.shape[2:])
-    par = np.tile(np.arange(-1, T - 1, dtype=np.int32), (n, 1))
-    S_ref = oracle.chain(S0, uv(x["k"]), uv(x["v"]), uv(x["alpha"]), uv(x["beta"]))
-    o_ref, _ = oracle.verify(S0, uv(x["q"]), uv(x["k"]), uv(x["v"]), uv(x["alpha"]), uv(x["beta"]), par)
+    assert bool(torch.isfinite(S_T.float()).all()) and bool(torch.isfinite(o.float()).all())
+    uv = lambda a: a.reshape(n, *a.shape[2:])[units]
+    par = np.tile(np.arange(-1, T - 1, dtype=np.int32), (len(units), 1))
+    S_ref = oracle.chain(S_chk, uv(x["k"]), uv(x["v"]), uv(x["alpha"]), uv(x["beta"]))
+    o_ref, _ = oracle.verify(S_chk, uv(x["q"]), uv(x["k"]), uv(x["v"]), uv(x["alpha"]), uv(x["beta"]), par)
     tol = TOL[dtype]
-    es = assert_close("S_T", S_T.float().cpu().numpy().reshape(n, 128, 128), S_ref, tol)
-    eo = assert_close("o", o.float().cpu().numpy().reshape(n, T, 128), o_ref, tol)
+    es = assert_close("S_T", S_T.float().cpu().numpy().reshape(n, 128, 128)[units], S_ref, tol)
+    eo = assert_close("o", o.float().cpu().numpy().reshape(n, T, 128)[units], o_ref, tol)
     say("[gpu] fast-decay prefill: max rel err S_T %.2e o %.2e" % (es, eo))
 
 

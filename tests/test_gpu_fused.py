@@ -136,18 +136,22 @@ def test_fused_round_sizes_differ(tw, Np, Nc, dtype):
     TwoRounds(mk(Np), mk(Nc), seed=Np + Nc).check_against_oracle(tw, "Np=%d Nc=%d %s" % (Np, Nc, dtype))
 
 
-@pytest.mark.parametrize("kind,Nc,depth", [("chain", 12, 12), ("chain", 17, 17), ("chain", 33, 33), ("chain", 64, 64),
-                                           ("tree", 64, 14)])
-def test_fused_current_round_solves(tw, kind, Nc, depth):
+@pytest.mark.parametrize("B,H", [(2, 3), (3, 43)])
+@pytest.mark.parametrize("kind,Nc,depth", [("tree", 16, 4), ("chain", 12, 12), ("chain", 17, 17), ("chain", 32, 32),
+                                           ("chain", 33, 33), ("chain", 64, 64), ("tree", 64, 14)])
+def test_fused_current_round_solves(tw, kind, Nc, depth, B, H):
     """The current round's tree taking each solve of T = (I + B)^{-1} inside
-    the fused call: chains of 12 and 17 and a 64-node tree of depth 14 (B read
-    one ancestor ahead), chains of 33 and 64 (the dense sweep, at 64 rows)."""
-    wp = wl.Workload("fused", 2, 3, 16, 128, 128, "bf16", "tree", 6, (4, 4, 2), (0.85, 0.999), (0.05, 0.95),
+    the fused call, in 129 units: a tree of depth 4 (registers), chains of 12
+    and 17 and a 64-node tree of depth 14 (B read one ancestor ahead), chains
+    of 32, 33 and 64 (the dense sweep, at 32 and 64 rows).  In 6 units drafts of
+    at most 48 nodes run the kernels of few units, which have one solve."""
+    wp = wl.Workload("fused", B, H, 16, 128, 128, "bf16", "tree", 6, (4, 4, 2), (0.85, 0.999), (0.05, 0.95),
                      16, "uniform_node")
     order = "chain_depth_0_to_N" if kind == "chain" else "uniform_node"
-    wc = wl.Workload(kind, 2, 3, Nc, 128, 128, "bf16", kind, depth, (1,) if kind == "chain" else (3,),
+    wc = wl.Workload(kind, B, H, Nc, 128, 128, "bf16", kind, depth, (1,) if kind == "chain" else (3,),
                      (0.85, 0.999), (0.05, 0.95), 16, order)
-    TwoRounds(wp, wc, seed=40 + Nc).check_against_oracle(tw, "current %s N=%d depth %d" % (kind, Nc, depth))
+    case = TwoRounds(wp, wc, seed=40 + Nc, check_units=wl.sample_units(wc, 6))
+    case.check_against_oracle(tw, "current %s N=%d depth %d, %d units" % (kind, Nc, depth, wc.units))
 
 
 @pytest.mark.parametrize("L", [9, 17, 40, 64])
@@ -197,7 +201,8 @@ def test_fused_matches_separate_calls(tw):
 
 def test_fused_empty_path_is_plain_verify(tw):
     """Nothing accepted: S_new = S_old bit for bit, and o, U equal treewy_verify
-    on S_old bit for bit (the update multiplies by 1 and adds 0)."""
+    on S_old bit for bit (the update multiplies by 1 and adds 0).  At every
+    node and unit count: the next test."""
     w = wl.scaled(wl.WORKLOADS[3], B=2, H=3)
     xp = wl.make_inputs(w, seed=51, cfg_key=351)
     xp["path_len"][:] = 0
@@ -241,15 +246,17 @@ def test_empty_path_and_one_chunk_are_verify_at_every_size(tw, B, H, dtype, stat
                 assert torch.equal(o, o_p), N
 
 
-def test_fused_bad_path_keeps_state(tw):
-    w = wl.scaled(wl.WORKLOADS[2], B=4, H=2)
+@pytest.mark.parametrize("cfg,H", [(2, 2), (2, 33), (3, 2), (3, 33)])
+def test_fused_bad_path_keeps_state(tw, cfg, H):
+    """16 and 64 nodes in 8 and 132 units: the kernel of few units (16 nodes in 8) and the others."""
+    w = wl.scaled(wl.WORKLOADS[cfg], B=4, H=H)
     xp = wl.make_inputs(w, seed=61, cfg_key=361)
     xp["path"][1, :2] = [0, 0]          # not increasing
     xp["path_len"][1] = 2
     xp["path_len"][2] = w.max_depth + 1  # longer than L_max
     xp["path"][3, 0] = w.N              # node out of range
     xp["path_len"][3] = max(int(xp["path_len"][3]), 1)
-    case = TwoRounds(w, w, seed=61, xp=xp)
+    case = TwoRounds(w, w, seed=61, xp=xp, check_units=wl.sample_units(w, 4))
     S_new, o, U, err, _ = case.run(tw)
     flags = err.cpu().numpy()
     assert flags[0] == 0 and list(flags[1:]) == [tw.FLAG_BAD_PATH] * 3
@@ -284,16 +291,17 @@ def test_fused_empty_current_draft(tw):
 
 
 @pytest.mark.parametrize("state", ["f32", "bf16"])
-@pytest.mark.parametrize("N", [16, 64])
-def test_fused_in_place_bit_identical(tw, state, N):
+@pytest.mark.parametrize("N,B,H", [(16, 3, 4), (64, 3, 4), (16, 3, 43), (32, 3, 43), (40, 3, 4)])
+def test_fused_in_place_bit_identical(tw, state, N, B, H):
     """S_new written over S_old gives bit for bit what the out-of-place call
     gives (each state row is read by the wave that writes it, before any of
     its lines is written), and the out-of-place call leaves S_old alone.
-    Both state types and both padded node counts (32 and 64)."""
-    w = wl.Workload("fused", 3, 4, N, 128, 128, "bf16", "tree", min(N, 8), (4, 4, 2), (0.85, 0.999),
+    Both state types; both padded node counts (32: 16 and 32 nodes in 129
+    units, and 64), and the kernels of few units (16 and 40 nodes in 12)."""
+    w = wl.Workload("fused", B, H, N, 128, 128, "bf16", "tree", min(N, 8), (4, 4, 2), (0.85, 0.999),
                     (0.05, 0.95), 16, "uniform_node")
     say("[gpu] fused in place: %s state, N=%d" % (state, N))
-    case = TwoRounds(w, w, seed=70 + N)
+    case = TwoRounds(w, w, seed=70 + N, check_units=wl.sample_units(w, 6))
     dp, dc = _dev(case.xp, w), _dev(case.xc, w)
     sdt = torch.float32 if state == "f32" else torch.bfloat16
     S_old = torch.from_numpy(case.S_old.reshape(w.B, w.H, 128, 128)).to(DEV).to(sdt)

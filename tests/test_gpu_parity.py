@@ -95,14 +95,17 @@ def spine_tree(N, anc, rng):
     return par
 
 
-@pytest.mark.parametrize("N,ancs", [(32, (9, 8, 17)), (32, (16, 0, 31)), (64, (8, 9, 16)), (64, (17, 16, 12))])
-def test_solve_depth_classes(tw, N, ancs):
+@pytest.mark.parametrize("H", [2, 44])
+@pytest.mark.parametrize("N,ancs", [(16, (9, 8, 15)), (32, (9, 8, 17)), (32, (16, 0, 31)), (64, (8, 9, 16)), (64, (17, 16, 12))])
+def test_solve_depth_classes(tw, N, ancs, H):
     """The three solves of T = (I + B)^{-1}, chosen per unit by its deepest
     node: at most 8 ancestors (entries of B gathered into registers), 9 to 16
     (B read one ancestor ahead), more (the dense blocked sweep).  Sequence b
     has exactly ancs[b] ancestors at its deepest node, so every boundary
-    meets the others within one launch."""
-    w = wl.Workload("spine", len(ancs), 2, N, 128, 128, "bf16", "tree", max(ancs) + 1, (2,), (0.85, 0.999),
+    meets the others within one launch.  (In 132 units, and with 64 nodes in
+    6; in 6 units 16 and 32 nodes run the kernels of few units, whose one
+    solve takes every depth.)"""
+    w = wl.Workload("spine", len(ancs), H, N, 128, 128, "bf16", "tree", max(ancs) + 1, (2,), (0.85, 0.999),
                     (0.05, 0.95), 16, "uniform_node")
     x = wl.make_inputs(w, seed=11, cfg_key=600 + N)
     rng = np.random.default_rng(N)
@@ -113,7 +116,9 @@ def test_solve_depth_classes(tw, N, ancs):
         x["path"][b] = -1
         x["path"][b, :len(nodes)] = nodes
         x["path_len"][b] = len(nodes)
-    run_and_check(tw, Case(w, seed=11, cfg_key=600 + N, inputs=x), "depth classes N=%d %s" % (N, ancs))
+    check = np.asarray([b * H + h for b in range(len(ancs)) for h in (0, H - 1)])
+    run_and_check(tw, Case(w, seed=11, cfg_key=600 + N, inputs=x, check_units=check),
+                  "depth classes N=%d %s, %d units" % (N, ancs, w.units))
 
 
 def test_fixed_width_tree_shapes(tw):
@@ -275,9 +280,11 @@ def test_path_too_long_and_bad_nodes_flagged(tw):
     assert path[1, :4].tolist() == [0, 1, 2, 3]
 
 
-def test_bad_parent_and_bad_path_flags(tw):
-    w = wl.scaled(wl.WORKLOADS[2], B=4, H=2)
-    case = Case(w, seed=14, cfg_key=2)
+@pytest.mark.parametrize("cfg,H", [(2, 2), (2, 33), (3, 2), (3, 33)])
+def test_bad_parent_and_bad_path_flags(tw, cfg, H):
+    """16 and 64 nodes in 8 and 132 units: the kernels of few units (16 nodes, and commit), and the others."""
+    w = wl.scaled(wl.WORKLOADS[cfg], B=4, H=H)
+    case = Case(w, seed=14, cfg_key=2, check_units=[0, w.units - 1])
     d = case.device()
     d["parent"][1, 5] = 9        # not an earlier node
     d["parent"][2, 3] = -7
@@ -289,7 +296,7 @@ def test_bad_parent_and_bad_path_flags(tw):
     err.zero_()
     good = wl.make_inputs(w, seed=14, cfg_key=2)["parent"]
     d["parent"] = torch.from_numpy(good).to(DEV)
-    d["path"][0, 0] = 40         # out of range
+    d["path"][0, 0] = 40 if w.N < 40 else 72   # out of range
     d["path_len"][3] = 99        # longer than L_max
     S_new = tw.treewy_commit(d["S0"], U, d["k"], d["alpha"], d["path"], d["path_len"], parent=d["parent"], err=err)
     torch.cuda.synchronize()

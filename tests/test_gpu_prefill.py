@@ -4,9 +4,11 @@ The reference is eq. 1 run over the chain: every token's output o_t = S_t q_t
 (the oracle's tree routine on a chain of T nodes) and the state after the last
 token (its chain routine).  Chunks of 32 bf16 tokens (64 fp32 tokens) with
 ragged tails, fp32 and bf16 inputs, fp32 and bf16 state, in place.  The
-lengths put each of the three solves of T = (I + B)^{-1} in the last chunk:
-at most 9 tokens (8 ancestors: registers), 10 to 17 (B read one ancestor
-ahead: 12, 49 = 32 + 17, 10, 81 = 64 + 17, 17) and more (the dense sweep).
+lengths give last chunks of at most 9, of 10 to 17 and of more tokens.  In 6
+units, as most cases here, the kernels are those of few units (at most 32 bf16
+tokens) and the one that splits a unit by columns; the other launch shapes, and
+the kernel of one workgroup per unit with its three solves, have a file of
+their own.
 """
 import numpy as np
 import pytest
@@ -85,8 +87,8 @@ def test_prefill_in_place_and_empty(tw):
 
 @pytest.mark.parametrize("T", [5, 12, 32])
 def test_prefill_equals_verify_then_commit(tw, T):
-    """One chunk of prefill (5, 12 or 32 bf16 tokens: each of the three
-    solves) is a chain verify plus a commit of the whole chain."""
+    """One chunk of prefill (5, 12 or 32 bf16 tokens) is a chain verify plus a
+    commit of the whole chain.  (At every number of units: the fused call's tests.)"""
     w = chain_workload(T, "bf16", B=3, H=2)
     x = wl.make_inputs(w, seed=9, cfg_key=790)
     S0 = torch.from_numpy(warm_state(w, np.arange(w.units), 9, 791).reshape(w.B, w.H, 128, 128)).to(DEV)
@@ -99,7 +101,7 @@ def test_prefill_equals_verify_then_commit(tw, T):
     path = torch.from_numpy(np.tile(np.arange(T, dtype=np.int32), (w.B, 1))).to(DEV)
     S2 = tw.treewy_commit(S0, U, k, al, path, torch.full((w.B,), T, dtype=torch.int32, device=DEV), parent=par)
     torch.cuda.synchronize()
-    assert torch.equal(o, o2)                      # the same verify kernel on the same chain
+    assert torch.equal(o, o2)                      # the same arithmetic on the same chain
     n = w.units
     assert_close("S_T vs commit", S_T.cpu().numpy().reshape(n, 128, 128), S2.cpu().numpy().reshape(n, 128, 128),
                  TOL["f32"])

@@ -7,8 +7,8 @@ after another; each workgroup's chunk waves and state waves meet at one
 barrier per 32-token chunk.  The lengths give one chunk (fp32 tokens), fewer
 chunks than chunk waves, one more, and ragged last chunks of 1, 16, 17 and 31
 tokens; the unit counts a ragged group of eight (a unit's workgroups are dealt
-out in groups of eight units), both edges of each rule, and several units per
-workgroup.  Sampled units are checked; the tolerance is the parity tests'.
+out in groups of eight units), both edges of each rule, several units per
+workgroup, and the sizes that the kernel of one workgroup per unit keeps.  Sampled units are checked; the tolerance is the parity tests'.
 """
 import numpy as np
 import pytest
@@ -35,6 +35,12 @@ CASES = [  # B, H, T, tokens, state
     (1, 257, 160, "bf16", "f32"), (10, 60, 177, "bf16", "bf16"), (9, 64, 319, "bf16", "f32"), (1, 257, 128, "bf16", "f32"),
     (1, 3, 17, "f32", "f32"), (1, 64, 97, "f32", "f32"), (5, 13, 48, "f32", "f32"), (2, 64, 130, "f32", "f32"),
     (3, 43, 70, "f32", "f32"),
+    # ... and the sizes kept by the kernel of one workgroup per unit, in its steady state: three and more chunks of 64 fp32
+    # tokens, two to four of 32 bf16 tokens past as many units as CUs
+    (3, 43, 200, "f32", "f32"), (1, 257, 321, "f32", "f32"), (3, 43, 129, "f32", "f32"), (1, 257, 97, "bf16", "bf16"),
+    (1, 257, 64, "bf16", "f32"), (5, 77, 128, "bf16", "f32"), (5, 77, 33, "bf16", "bf16"),
+    # (its three solves, by the last chunk's ancestors: above at most 8 or more than 16, here 9 to 16)
+    (3, 43, 81, "f32", "f32"), (5, 77, 49, "bf16", "f32"), (5, 77, 44, "bf16", "bf16"),
 ]
 
 

@@ -1,8 +1,8 @@
 """The kernels of few units (drafts of at most 48 nodes, chains of at most 32
 tokens, commits), vs the float64 oracle: every wave on its own 16 columns, so
 the cases are the node counts around the four-node lane groups and the 16-node
-tiles, chains and trees, each type, both sides of the unit counts where the
-other kernels take over, ragged groups of eight units, long and bad paths, and
+tiles, chains and trees, each type, both sides of the unit count where the
+other kernels take over (128 of 256 CUs), ragged groups of eight units, long and bad paths, and
 bad parents."""
 import numpy as np
 import pytest
@@ -153,10 +153,11 @@ def test_long_paths_cost_no_more_than_in_one_unit_more(tw, dtype):
     assert best[0] <= 1.15 * best[1], best
 
 
-@pytest.mark.parametrize("N", [9, 25, 40])
-def test_malformed(tw, N):
-    """A bad parent counts as -1, a bad path keeps the state, each with its flag and only for its sequence."""
-    w, case = make(3, 2, N, "chain", "bf16", 14)
+@pytest.mark.parametrize("N,H", [(9, 2), (25, 2), (40, 2), (64, 2), (9, 43), (25, 43), (40, 43)])
+def test_malformed(tw, N, H):
+    """A bad parent counts as -1, a bad path keeps the state, each with its flag and only for its sequence; in 129
+    units, and with 64 nodes, by the kernels that these take over from."""
+    w, case = make(3, H, N, "chain", "bf16", 14, check=[b * H + h for b in range(3) for h in (0, H - 1)])
     par = case.x["parent"].copy()
     par[1, 4], par[1, 7] = 4, -3
     case.x["parent"][1, 4] = case.x["parent"][1, 7] = -1
