@@ -22,6 +22,24 @@ __device__ __forceinline__ void split4(f32x4 x, uint2 &hi, uint2 &lo) {
     lo.y = pack_bf2(x[2] - __builtin_bit_cast(float, hi.y << 16), x[3] - __builtin_bit_cast(float, hi.y & 0xffff0000u));
 }
 
+// Four floats -> bf16 hi + mid + lo, exactly (24 bits; past the type's range of exponents lo may round).
+__device__ __forceinline__ void split4(f32x4 x, uint2 &hi, uint2 &mid, uint2 &lo) {
+    auto rest = [](f32x4 &y, uint2 h) {
+        y[0] -= __builtin_bit_cast(float, h.x << 16);
+        y[1] -= __builtin_bit_cast(float, h.x & 0xffff0000u);
+        y[2] -= __builtin_bit_cast(float, h.y << 16);
+        y[3] -= __builtin_bit_cast(float, h.y & 0xffff0000u);
+    };
+    hi = make_uint2(pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]));
+    rest(x, hi);
+    mid = make_uint2(pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]));
+    rest(x, mid);
+    lo = make_uint2(pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]));
+}
+
+// Two values of four contraction entries each, in the two halves of a lane group's eight slots.
+__device__ __forceinline__ bf16x8 both8(uint2 x, uint2 y) { return __builtin_bit_cast(bf16x8, make_uint4(x.x, x.y, y.x, y.y)); }
+
 // Four contraction entries of a lane group as the low half of its eight slots, the others empty.
 __device__ __forceinline__ bf16x8 low8(uint2 x) { return __builtin_bit_cast(bf16x8, make_uint4(x.x, x.y, 0u, 0u)); }
 

@@ -512,7 +512,11 @@ __device__ __forceinline__ void transpose_groups(float (&x)[4]) {
 // q (a transpose across the lane groups before and after turns the gram's
 // layout into rows and back); T itself is not formed: U comes by forward
 // substitution over the tiles, U_a = T_a (R_a - sum over b < a of B_ab U_b), whose
-// operands B_ab and A_ab are the gram tiles as the accumulators hold them.
+// operands B_ab and A_ab are the gram tiles as the accumulators hold them.  Past
+// the first tile T, B, R and U stand as three bf16 each in this solve (24 bits:
+// with keys that lie close together the sum cancels most of R, and in pairs the
+// error of U was up to 1.6 times verify.hip's): six products in three
+// instructions, two to the halves of the contraction (0.1 us more at 48 nodes).
 template <bool SBF, int MODE, int NT>
 __global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void tiles_kernel(
     const void *S0, const void *__restrict__ q_, const void *__restrict__ k_, const void *__restrict__ v_,
@@ -614,7 +618,8 @@ __global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void til
 
     // ---- gram tiles: lane t = 16 a + l16, rows i = 16 bb + 4 g + r, bb <= a --------
     constexpr int PAIRS = NT * (NT + 1) / 2;             // tile (a, bb) at a (a + 1) / 2 + bb
-    uint2 Bh[PAIRS], Bl[PAIRS], Ah[PAIRS], Al[PAIRS];    // -B off the diagonal, and A, as operands
+    uint2 Bh[PAIRS], Bm[PAIRS], Bl[PAIRS];               // -B off the diagonal, and A, as operands
+    uint2 Ah[PAIRS], Al[PAIRS];
     float Bd[4][4] = {};                                 // B's diagonal tiles
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
@@ -649,13 +654,13 @@ __global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void til
 #pragma unroll
                 for (int r = 0; r < 4; ++r) Bd[a][r] = Bt[r];
             } else {
-                split4(-Bt, Bh[p], Bl[p]);
+                split4(-Bt, Bh[p], Bm[p], Bl[p]);
             }
         }
     }
 
     // ---- the diagonal blocks of T: block q's rows in lane group q ------------------
-    uint2 Th[4], Tl[4];
+    uint2 Th[4], Tm[4], Tl[4];
     {
         float bb[16], r[16];
 #pragma unroll
@@ -680,7 +685,7 @@ __global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void til
             for (int q = 0; q < 4; ++q) t[q][e] = x[q];
         }
 #pragma unroll
-        for (int q = 0; q < NT; ++q) split4(t[q], Th[q], Tl[q]);
+        for (int q = 0; q < NT; ++q) split4(t[q], Th[q], Tm[q], Tl[q]);
     }
 
     // ---- fused: the previous round's path into the state, and the state out --------
@@ -720,9 +725,14 @@ __global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void til
         acc = mma16(low8(ah), low8(xl), acc);
         return mma16(low8(alo), low8(xh), acc);
     };
+    auto product3 = [&](uint2 ah, uint2 am, uint2 alo, uint2 xh, uint2 xm, uint2 xl, f32x4 acc) {
+        acc = mma16(both8(ah, alo), both8(xl, xh), acc);
+        acc = mma16(both8(ah, am), both8(xm, xm), acc);
+        return mma16(both8(ah, am), both8(xh, xh), acc);
+    };
     const rsrc_t ru = make_rsrc(MODE == PREFILL ? nullptr : U + node0 * D, MODE == PREFILL ? 0 : N * D * 4);
     const rsrc_t ro = make_rsrc(static_cast<In *>(o_) + node0 * D, N * ROW);
-    uint2 uh[NT], ul[NT];
+    uint2 uh[NT], um[NT], ul[NT];
     f32x4 u32[MODE == PREFILL ? NT : 1];
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
@@ -738,18 +748,22 @@ __global__ __launch_bounds__(64 * NW, MODE == FUSED && NT == 3 ? 1 : 2) void til
             pq[a][r] *= gr;
         }
 #pragma unroll
-        for (int bb = 0; bb < a; ++bb) R = product(Bh[a * (a + 1) / 2 + bb], Bl[a * (a + 1) / 2 + bb], uh[bb], ul[bb], R);
-        uint2 rh, rl;
-        split4(R, rh, rl);
-        const f32x4 uu = product(Th[a], Tl[a], rh, rl, f32x4{});
+        for (int bb = 0; bb < a; ++bb) {
+            const int p = a * (a + 1) / 2 + bb;
+            R = product3(Bh[p], Bm[p], Bl[p], uh[bb], um[bb], ul[bb], R);
+        }
+        uint2 rh, rm, rl;
+        split4(R, rh, rm, rl);
+        // (the first tile as small_kernel has it: the same bits)
+        const f32x4 uu = a == 0 ? product(Th[a], Tm[a], rh, rm, f32x4{}) : product3(Th[a], Tm[a], Tl[a], rh, rm, rl, f32x4{});
         if constexpr (MODE == PREFILL) u32[a] = uu;
         else
 #pragma unroll
             for (int r = 0; r < 4; ++r) st_f32<CACHED>(ru, ((16 * a + 4 * g + r) * D + col) * 4, uu[r]);
-        split4(uu, uh[a], ul[a]);
+        split4(uu, uh[a], um[a], ul[a]);
         f32x4 oo = pq[a];
 #pragma unroll
-        for (int bb = 0; bb <= a; ++bb) oo = product(Ah[a * (a + 1) / 2 + bb], Al[a * (a + 1) / 2 + bb], uh[bb], ul[bb], oo);
+        for (int bb = 0; bb <= a; ++bb) oo = product(Ah[a * (a + 1) / 2 + bb], Al[a * (a + 1) / 2 + bb], uh[bb], um[bb], oo);
 #pragma unroll
         for (int r = 0; r < 4; r += 2) {
             const int off = ((16 * a + 4 * g + r) * D + col) * (int)sizeof(In);
