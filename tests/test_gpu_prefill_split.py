@@ -73,3 +73,32 @@ def test_prefill_launch_shapes(tw, B, H, T, dtype, state, in_place):
     o_ref, _ = oracle.verify(S0, uv(x["q"]), uv(x["k"]), uv(x["v"]), uv(x["alpha"]), uv(x["beta"]), par)
     assert_close("S_T", S_T.float().cpu().numpy().reshape(w.units, 128, 128)[units], S_ref, TOL[dtype])
     assert_close("o", o.float().cpu().numpy().reshape(w.units, T, 128)[units], o_ref, TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype,T,H", [("bf16", 49, 385), ("f32", 17, 129), ("f32", 49, 129)])
+def test_close_keys(tw, dtype, T, H):
+    """A last chunk of 17 tokens with keys close together and gates near one, where what the solve holds in few bits
+    shows: 64 units, split by columns, against the same 64 among `H` in the kernel of one workgroup per unit.  Same inputs,
+    so the errors against 64 bits compare closely: 1.00 of it at most, and 1.04 to 1.07 with the solve's
+    off-diagonal block from pairs of bf16."""
+    w = wl.Workload("prefill", 1, H, T, 128, 128, dtype, "chain", T, (1,), (0.9999, 0.9999), (0.9, 1.0), 16, "chain_depth_0_to_N")
+    x = wl.make_inputs(w, seed=33, cfg_key=3300)
+    rng = np.random.default_rng(33)
+    k = rng.standard_normal((1, H, 1, 128)) + 0.3 * rng.standard_normal((1, H, T, 128))
+    k = (k / np.linalg.norm(k, axis=-1, keepdims=True)).astype(np.float32)
+    x["k"] = wl.round_to_bf16(k) if dtype == "bf16" else k
+    S0 = (0.1 * rng.standard_normal((1, H, 128, 128))).astype(np.float32)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    dev = lambda a, d=torch.float32: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(DEV).to(d)
+    uv = lambda a: a[0, :64]
+    S_ref = oracle.chain(uv(S0), uv(x["k"]), uv(x["v"]), uv(x["alpha"]), uv(x["beta"]))
+
+    def err(n):
+        S_T, _ = tw.treewy_chain_prefill(dev(S0[:, :n]), *[dev(x[m][:, :n], dt) for m in ("q", "k", "v")],
+                                         *[dev(x[m][:, :n]) for m in ("alpha", "beta")])
+        torch.cuda.synchronize()
+        return np.linalg.norm(S_T[0, :64].cpu().numpy() - S_ref) / np.linalg.norm(S_ref)
+
+    split, unit = err(64), err(H)
+    say("[gpu] close keys, %s tokens, T=%d: error of S_T %.3g split, %.3g whole" % (dtype, T, split, unit))
+    assert split <= 1.02 * unit
