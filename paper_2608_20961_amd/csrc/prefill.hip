@@ -459,9 +459,12 @@ __global__ __launch_bounds__(64 * launched_waves<NS>(PW), (launched_waves<NS>(PW
             if constexpr (PW >= 3) step_end();
             // T = (I + B)^{-1}: the two 16-row diagonal blocks by the sweep, on
             // lanes 0 to 31, then the block below them, T10 = -T1 (B10 T0), on
-            // the matrix cores, B10 and B10 T0 as three bf16 each (in pairs a
-            // last chunk of 17 tokens with close keys came out 4 to 7% further
-            // off than by verify.hip).  The planes go over B's fp32 rows, read before.
+            // the matrix cores, in pairs of bf16 as verify.hip has it for more
+            // than 16 ancestors.  For at most 16 that kernel's solve is in
+            // fp32: there B10 and B10 T0 stand as three bf16 each (in pairs a last
+            // chunk of 17 tokens with close keys came out 4 to 7% further off;
+            // in three everywhere whole units took 1 to 2% longer).  The planes
+            // go over B's fp32 rows, read before.
             // Lanes 32 to 63 sweep the zeros above the diagonal blocks and
             // write these, and zeros where T10 goes.
             {
@@ -492,23 +495,35 @@ __global__ __launch_bounds__(64 * launched_waves<NS>(PW), (launched_waves<NS>(PW
                 // Rows 4 g + e of T0, column tl (a transposed read), and of T1, row tl.
                 const unsigned char *t0 = th + plane_at(4 * g + (tl >> 2), 4 * (tl & 3));
                 const unsigned char *t1 = th + plane_at(16 + tl, 16 + 4 * g);
-                auto twice = [](uint2 x) { return both8(x, x); };   // (against two parts of the other operand)
-                const bf16x8 t0h = twice(__builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)t0)));
+                const bf16x8 t0h = low8(__builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)t0)));
                 const bf16x8 t0l =
-                    twice(__builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(t0 + L::PLANE))));
-                const bf16x8 t1h = twice(*reinterpret_cast<const uint2 *>(t1));
-                const bf16x8 t1l = twice(*reinterpret_cast<const uint2 *>(t1 + L::PLANE));
-                uint2 hi, mid, lo;
-                split4(b10, hi, mid, lo);
+                    low8(__builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(t0 + L::PLANE))));
+                const bf16x8 t1h = low8(*reinterpret_cast<const uint2 *>(t1));
+                const bf16x8 t1l = low8(*reinterpret_cast<const uint2 *>(t1 + L::PLANE));
+                // (in pairs; the third parts where at most 16 tokens precede one, see above)
+                const bool third = n <= 17;
+                uint2 hi, lo, rest;
+                split4(b10, hi, lo);
                 f32x4 acc = {};
-                acc = mma16(low8(lo), t0h, acc);
-                acc = mma16(both8(hi, mid), t0l, acc);
-                acc = mma16(both8(hi, mid), t0h, acc);   // B10 T0: rows 4 g + e, column tl
-                split4(acc, hi, mid, lo);
+                acc = mma16(low8(hi), t0h, acc);
+                acc = mma16(low8(hi), t0l, acc);
+                acc = mma16(low8(lo), t0h, acc);         // B10 T0: rows 4 g + e, column tl
+                if (third) {
+                    split4(b10, hi, lo, rest);
+                    acc = mma16(low8(lo), t0l, acc);
+                    acc = mma16(low8(rest), t0h, acc);
+                }
+                const f32x4 b10t0 = acc;
+                split4(b10t0, hi, lo);
                 acc = f32x4{};
+                acc = mma16(t1h, low8(hi), acc);
                 acc = mma16(t1h, low8(lo), acc);
-                acc = mma16(t1l, both8(hi, mid), acc);
-                acc = mma16(t1h, both8(hi, mid), acc);
+                acc = mma16(t1l, low8(hi), acc);
+                if (third) {
+                    split4(b10t0, hi, lo, rest);
+                    acc = mma16(t1l, low8(lo), acc);
+                    acc = mma16(t1h, low8(rest), acc);
+                }
                 split4(-acc, hi, lo);
                 unsigned char *w = th + plane_at(16 + 4 * g, tl);   // (rows 16 + 4 g + e: the same granule)
 #pragma unroll

@@ -126,7 +126,8 @@ struct State {
     }
 };
 
-// x[i] += u k[i], i = 0 .. 15, where k[2 j], k[2 j + 1] are the values k0, k1 of lane L + j of each row of 16 lanes (see fmac_bcast).
+// x[i] += u k[i], i = 0 .. 15, where k[2 j], k[2 j + 1] are the values k0, k1 of
+// lane L + j of each row of 16 lanes (see fmac_bcast).
 template <int L> __device__ __forceinline__ void rank1_half(float (&x0)[8], float (&x1)[8], float k0, float k1, float u) {
 #define TW_F(n, m, j) "v_fmac_f32_dpp %" #n ", %" #m ", %[u] row_newbcast:%[i" #j "] row_mask:0xf bank_mask:0xf\n\t"
     asm("s_nop 1\n\t" TW_F(0, 16, 0) TW_F(1, 17, 0) TW_F(2, 16, 1) TW_F(3, 17, 1) TW_F(4, 16, 2) TW_F(5, 17, 2)
