@@ -75,6 +75,10 @@ class Wrapped(torch.Tensor):
 def case():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    return inputs()
+
+
+def inputs():
     from paper_2608_20961_amd import treewy as tw
     g = torch.Generator(device="cuda").manual_seed(4)
     B, H, N = 2, 3, 9
@@ -184,9 +188,17 @@ def test_a_pointer_that_cannot_be_taken_raises(case, name):
 @pytest.mark.gpu
 def test_a_failed_allocation_never_commits_twice(case):
     """Memory that runs out at any one allocation of an in-place fused call: the state is the old one or the
-    committed one, and the committed one where the call returned (a call repeated after its launch commits twice)."""
-    _testcapi = pytest.importorskip("_testcapi")
-    tw, x = case
+    committed one, and the committed one where the call returned (a call repeated after its launch commits twice).
+    In a process of its own, which such a failure may end anywhere else as well."""
+    pytest.importorskip("_testcapi")
+    code = "from tests.test_binding import commit_with_failing_allocations as f; f()"
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "raised in" in r.stdout, r.stderr[-2000:]
+
+
+def commit_with_failing_allocations():
+    import _testcapi
+    tw, x = inputs()
     B, H, N = x["alpha"].shape
     ver = [x[n] for n in ("q", "k", "v", "alpha", "beta", "parent")]
     _, U = tw.treewy_verify(x["S0"], *ver)
